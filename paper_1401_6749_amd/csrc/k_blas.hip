@@ -407,8 +407,9 @@ void launch_accum_x(const Geom &g, char *x64, size_t s64, const char *x32_in, ch
         hipLaunchKernelGGL(k_accum_x, dim3(nblk_of(g), n), dim3(BLOCK), 0, s, g, x64, x32_in, x32_zero, s64, s32);
 }
 
-// per-tile |f|^2 of one FP64 half field: partial[tile], 64-site tiles
-__global__ __launch_bounds__(BLOCK) void k_norm_partial(Geom g, const char *f, double *partial)
+// per-tile |f|^2 of one FP64 half field: partial[tile], 64-site tiles (the
+// partials beyond the last tile, of a walk with partly filled waves, are zero)
+__global__ __launch_bounds__(BLOCK) void k_norm_partial(Geom g, const char *f, double *partial, int ntile)
 {
     const int cb = blockIdx.x * BLOCK + threadIdx.x;
     double part = 0.0;
@@ -420,12 +421,13 @@ __global__ __launch_bounds__(BLOCK) void k_norm_partial(Geom g, const char *f, d
     }
     part = wave_sum(part);
     const int tile = cb / TILE;
-    if ((threadIdx.x & 63) == 0 && tile < ntile_of(g)) partial[tile] = part;
+    if ((threadIdx.x & 63) == 0 && tile < ntile) partial[tile] = part;
 }
 
 void launch_norm_partial(const Geom &g, const char *f, double *partial, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_norm_partial, dim3(nblk_of(g)), dim3(BLOCK), 0, s, g, f, partial);
+    const int nt = ntile_of(g);
+    hipLaunchKernelGGL(k_norm_partial, dim3((nt * TILE + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, g, f, partial, nt);
 }
 
 __global__ __launch_bounds__(BLOCK) void k_site_diag(Geom g, int mode, double a, const char *in, char *out)

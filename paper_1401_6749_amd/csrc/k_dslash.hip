@@ -13,6 +13,7 @@
 #include "tm_launch.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <type_traits>
 
@@ -398,11 +399,11 @@ __device__ __forceinline__ void transport_pk(const LinkPk &u, const cpx<float> h
     }
 }
 
-// One FP16 neighbour n of site s on packed operands (see above); raw holds
-// the neighbour's stored words.
+// hop_w of one FP16 neighbour n of site s on packed operands (see above); raw
+// holds the neighbour's stored words.
 template <int MU, bool FWD, bool DAG>
-__device__ __forceinline__ void hop_compute_pk(const DslashArgs &A, __amdgpu_buffer_rsrc_t gauge, const Site &s, int n,
-                                               const RawHalf<P16, float> &raw, cpx<float> acc[12])
+__device__ __forceinline__ void hop_w_pk(const DslashArgs &A, __amdgpu_buffer_rsrc_t gauge, const Site &s, int n,
+                                         const RawHalf<P16, float> &raw, cpx<float> w[6])
 {
     const int vh = A.g.vh;
     constexpr int S = (FWD != DAG) ? -1 : 1;
@@ -416,27 +417,26 @@ __device__ __forceinline__ void hop_compute_pk(const DslashArgs &A, __amdgpu_buf
     cpx<float> h0[3], h1[3];
 #pragma unroll
     for (int c = 0; c < 3; c++) project_pk<MU, S>(p, c, sc, h0[c], h1[c]);
-    cpx<float> w[6];
-    {
-        float wr[3], wi[3];
-        transport_pk<FWD>(u, h0, wr, wi);
+    float wr[3], wi[3];
+    transport_pk<FWD>(u, h0, wr, wi);
 #pragma unroll
-        for (int a = 0; a < 3; a++) w[a] = cpx<float>{wr[a], wi[a]};
-        transport_pk<FWD>(u, h1, wr, wi);
+    for (int a = 0; a < 3; a++) w[a] = cpx<float>{wr[a], wi[a]};
+    transport_pk<FWD>(u, h1, wr, wi);
 #pragma unroll
-        for (int a = 0; a < 3; a++) w[3 + a] = cpx<float>{wr[a], wi[a]};
-    }
-    accum<float, MU, S>(acc, w);
+    for (int a = 0; a < 3; a++) w[3 + a] = cpx<float>{wr[a], wi[a]};
 }
 
-// The two transported spin rows of neighbour n of site s (FP64/FP32 storage),
-// before they are added into the output spinor: the projector, the link
+// The two transported spin rows of neighbour n of site s before they are added into the output spinor: the projector, the link
 // product and the antiperiodic sign of a temporal hop that wraps.  For the
 // backward t neighbour only s.t is read.
 template <class T, int SP, int MU, bool FWD, bool DAG, class RawT>
 __device__ __forceinline__ void hop_w(const DslashArgs &A, __amdgpu_buffer_rsrc_t gauge, const Site &s, int n,
                                       const RawT &raw, cpx<T> w[6])
 {
+    if constexpr (SP == P16 && std::is_same<RawT, RawHalf<P16, float>>::value) {
+        hop_w_pk<MU, FWD, DAG>(A, gauge, s, n, raw, w);
+        return;
+    }
     constexpr int S = (FWD != DAG) ? -1 : 1;
     Link<T> L;
     load_link<SP, T>(gauge, A.g.vh, FWD ? A.out_par : 1 - A.out_par, MU, FWD ? s.cb : n, L);
@@ -454,10 +454,6 @@ template <class T, int SP, int MU, bool FWD, bool DAG, class RawT>
 __device__ __forceinline__ void hop_compute(const DslashArgs &A, __amdgpu_buffer_rsrc_t gauge, const Site &s, int n,
                                             const RawT &raw, cpx<T> acc[12])
 {
-    if constexpr (SP == P16 && std::is_same<RawT, RawHalf<P16, float>>::value) {
-        hop_compute_pk<MU, FWD, DAG>(A, gauge, s, n, raw, acc);
-        return;
-    }
     constexpr int S = (FWD != DAG) ? -1 : 1;
     cpx<T> w[6];
     hop_w<T, SP, MU, FWD, DAG, RawT>(A, gauge, s, n, raw, w);
@@ -720,20 +716,11 @@ __global__ __launch_bounds__(BLOCK, dslash_waves<SP>()) void k_dslash(const Dsla
 // walk_nbuf).  Only neighbours outside the chunk (the z planes above and
 // below, and y rows at the chunk's edges) are read from global memory, where
 // the blocks working on those chunks have just fetched them into L2.  The
-// chunk shape is picked on the host to minimise the halo; each 64-thread
-// wave covers one 64-site reduction tile.  The arithmetic per neighbour is
+// chunk shape is picked on the host (walk_plan); each wave is one reduction
+// tile.  The arithmetic per neighbour is
 // that of k_dslash, in the same order (backward t first, forward t last), so
 // both buffer schemes give the same bits.
 // ---------------------------------------------------------------------------
-#ifndef TM_WALK_MAX_HALF
-#define TM_WALK_MAX_HALF 256
-#endif
-#ifndef TM_WALK_MAX_F32
-#define TM_WALK_MAX_F32 256
-#endif
-#ifndef TM_WALK_MAX_F64
-#define TM_WALK_MAX_F64 256
-#endif
 // LDS buffers per block: one timeslice or two.  With two, the thread's own
 // site of t+1 goes into the second buffer while the block still reads
 // timeslice t, and the buffer of t-1 serves the backward t neighbour: one
@@ -754,23 +741,16 @@ constexpr int walk_nbuf()
 {
     return SP == P64 ? TM_WALK_NB_F64 : SP == P32 ? TM_WALK_NB_F32 : 2;
 }
-// largest chunk (threads per block) per storage precision: FP64 256 sites
-// (48 KB, one buffer), FP32 256 (24 KB, one buffer), FP16/BF16 256 (26 KB,
-// two buffers: 512-site chunks, 52 KB, read fewer halo neighbours, 0.75
-// against 1.0 per site at 32^3x64, but their eight-wave blocks start less
-// readily beside a concurrent stream's kernels: TSM step 273.9 against 278.7
-// sources/s, same bits)
-template <int SP>
-constexpr int walk_max()
-{
-    return SP == P64 ? TM_WALK_MAX_F64 : SP == P32 ? TM_WALK_MAX_F32 : TM_WALK_MAX_HALF;
-}
-
+// A chunk has at most 256 sites (WALK_MAX): FP64 48 KB and FP32 24 KB with one
+// buffer, FP16/BF16 26 KB with two (512-site chunks, 52 KB, read fewer halo
+// neighbours, 0.75 against 1.0 per site at 32^3x64, but their eight-wave
+// blocks start less readily beside a concurrent stream's kernels: TSM step
+// 273.9 against 278.7 sources/s, same bits).
 template <int SP>
 struct WalkBuf;
 template <>
 struct WalkBuf<P64> {
-    u32x4 q[walk_nbuf<P64>()][12][walk_max<P64>()];
+    u32x4 q[walk_nbuf<P64>()][12][WALK_MAX];
     __device__ __forceinline__ void get(int b, int d, Raw<P64, double> &r) const
     {
 #pragma unroll
@@ -784,7 +764,7 @@ struct WalkBuf<P64> {
 };
 template <>
 struct WalkBuf<P32> {
-    u32x4 q[walk_nbuf<P32>()][6][walk_max<P32>()];
+    u32x4 q[walk_nbuf<P32>()][6][WALK_MAX];
     __device__ __forceinline__ void get(int b, int d, Raw<P32, float> &r) const
     {
 #pragma unroll
@@ -798,8 +778,8 @@ struct WalkBuf<P32> {
 };
 template <int SP>
 struct WalkBufHalf {
-    u32x4 q[2][3][walk_max<SP>()];
-    float sc[2][walk_max<SP>()];
+    u32x4 q[2][3][WALK_MAX];
+    float sc[2][WALK_MAX];
     __device__ __forceinline__ void get(int b, int d, RawHalf<SP, float> &r) const
     {
 #pragma unroll
@@ -820,7 +800,8 @@ struct WalkBuf<PBF> : WalkBufHalf<PBF> {};
 
 struct WalkPos {
     int buf;     // LDS buffer holding the current timeslice
-    int yy, zz;  // the thread's row and plane within the chunk
+    int l;       // the thread's site within the chunk (idle lanes: the last one)
+    int yy, zz;  // its row and plane within the chunk
 };
 
 // Halo prefetch of the half-precision walk (bit 0: z halo, bit 1: y halo):
@@ -846,11 +827,11 @@ __device__ __forceinline__ void walk_dir(const DslashArgs &A, const HopRes &R, c
     const int n = nbr<MU, FWD ? 1 : -1>(A.g, s);
     if constexpr (MU == 3) {
         RawT raw;
-        W.get(w.buf ^ 1, threadIdx.x, raw);
+        W.get(w.buf ^ 1, w.l, raw);
         hop_compute<T, SP, MU, FWD, DAG, RawT>(A, R.gauge, s, n, raw, acc);
     } else {
         RawT raw;
-        const int l = (int)threadIdx.x;
+        const int l = w.l;
         bool in = true;
         int d = l;
         if (MU == 0) {
@@ -892,8 +873,11 @@ constexpr int walk_waves()
 
 // SRC bit 1: the site-local input is eta decoded from Z4 codes (the
 // reconstruction of noise solves), as in k_dslash.
-template <int SP, bool DAG, int EPI, bool IN2, bool SLOT, bool NT, int SRC = 0, int PO = SP>
-__global__ __launch_bounds__(walk_max<SP>(), (walk_waves<SP, EPI>())) void k_dslash_walk(const DslashArgs A)
+// PART: the chunk's last wave is partly filled; its lanes beyond the last site
+// follow that site and write nothing (a variant of its own, because the masks
+// cost the full chunks 1.5% of the 12-RHS FP16 hop).
+template <int SP, bool DAG, int EPI, bool IN2, bool SLOT, bool NT, int SRC = 0, int PO = SP, bool PART = false>
+__global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_walk(const DslashArgs A)
 {
     using T = typename Real<SP>::T;
     using RawT = typename RawSel<SP, T>::type;
@@ -912,7 +896,10 @@ __global__ __launch_bounds__(walk_max<SP>(), (walk_waves<SP, EPI>())) void k_dsl
     const int vh = g.vh, lt = g.L[3], tw = A.twalk;
     const int ncy = g.L[1] / A.wcy, chunks = ncy * (g.L[2] / A.wcz);
     const int tb = sb / chunks, c = sb - tb * chunks;
-    const int l = (int)threadIdx.x, xh = l % g.lxh, rz = l / g.lxh;
+    const int cs = A.wcy * A.wcz * g.lxh;
+    const bool live = !PART || (int)threadIdx.x < cs;
+    const int l = live ? (int)threadIdx.x : cs - 1;
+    const int xh = l % g.lxh, rz = l / g.lxh;
     const int yy = rz % A.wcy, zz = rz / A.wcy;
     // the thread's site within a timeslice
     const int o = xh + g.sy * ((c % ncy) * A.wcy + yy) + g.sz * ((c / ncy) * A.wcz + zz);
@@ -950,10 +937,10 @@ __global__ __launch_bounds__(walk_max<SP>(), (walk_waves<SP, EPI>())) void k_dsl
         if constexpr (NB == 1) {
             const Site s0 = site_of(g, t0 * g.st + o, A.out_par);
             hop_w<T, SP, 3, false, DAG, RawT>(A, R.gauge, s0, ((t0 + lt - 1) % lt) * g.st + o, r0, carry);
-            W.put(0, threadIdx.x, r1);
-        } else {
-            W.put(1, threadIdx.x, r0);
-            W.put(0, threadIdx.x, r1);
+            if (live) W.put(0, l, r1);
+        } else if (live) {
+            W.put(1, l, r0);
+            W.put(0, l, r1);
         }
     }
     __syncthreads();
@@ -962,7 +949,7 @@ __global__ __launch_bounds__(walk_max<SP>(), (walk_waves<SP, EPI>())) void k_dsl
         const int cb = t * g.st + o;
         RawT nxt;
         if constexpr (NB != 1) nxt.load(R.in, 0, vh, ((t + 1) % lt) * g.st + o);
-        const WalkPos w{NB == 1 ? 0 : (k & 1), yy, zz};
+        const WalkPos w{NB == 1 ? 0 : (k & 1), l, yy, zz};
         const Site s = site_of(g, cb, A.out_par);
         cpx<T> acc[12];
 #pragma unroll
@@ -993,8 +980,8 @@ __global__ __launch_bounds__(walk_max<SP>(), (walk_waves<SP, EPI>())) void k_dsl
                 // back, then replaced by its site of t+1; the backward hop
                 // reads only the output's t
                 RawT own;
-                W.get(0, threadIdx.x, own);
-                W.put(0, threadIdx.x, nxt);
+                W.get(0, l, own);
+                if (live) W.put(0, l, nxt);
                 Site s1 = s;
                 s1.t = t + 1 == lt ? 0 : t + 1;
                 hop_w<T, SP, 3, false, DAG, RawT>(A, R.gauge, s1, cb, own, carry);
@@ -1005,7 +992,7 @@ __global__ __launch_bounds__(walk_max<SP>(), (walk_waves<SP, EPI>())) void k_dsl
             // neighbour now and the next step's spatial neighbours), so nxt is
             // not held in registers through the other seven neighbours.
             walk_dir<SP, 3, false, DAG>(A, R, s, W, w, acc, hy, hz, pf);
-            W.put(w.buf ^ 1, threadIdx.x, nxt);
+            if (live) W.put(w.buf ^ 1, l, nxt);
 #pragma unroll 1
             for (int d = 0; d < 7; d++) {
                 switch (__builtin_amdgcn_readfirstlane(d)) {
@@ -1022,11 +1009,13 @@ __global__ __launch_bounds__(walk_max<SP>(), (walk_waves<SP, EPI>())) void k_dsl
         // next timeslice's halo, while its owners are reading it
         if constexpr (PF != 0)
             if (k + 1 < tw) halo_load(t + 1);
-        const double part = epilogue<SP, EPI, IN2, SRC, NT, PO>(A, slot, cb, acc, kappa, a, alpha);
+        double part = 0.0;
+        if (live) part = epilogue<SP, EPI, IN2, SRC, NT, PO>(A, slot, cb, acc, kappa, a, alpha);
         if constexpr (EPI != EPI_PLAIN) {
-            // one wave = one 64-site reduction tile
+            // one wave = one reduction tile
             const double v = wave_sum(part);
-            if ((threadIdx.x & 63) == 0) A.partial[(size_t)slot * A.ntile + cb / TILE] = v;
+            if ((threadIdx.x & 63) == 0)
+                A.partial[(size_t)slot * A.ntile + (t * chunks + c) * (blockDim.x >> 6) + (threadIdx.x >> 6)] = v;
         }
         __syncthreads();
     }
@@ -1054,13 +1043,6 @@ inline int dslash_twalk()
     return tw;
 }
 
-// integer tuning knob from the environment (read once)
-inline int env_knob(const char *name, int dflt)
-{
-    const char *e = getenv(name);
-    return e ? atoi(e) : dflt;
-}
-
 // lanes per site: one per slot up to 4 (TM_DSLASH_R caps it)
 inline int lanes_per_site(int nslot)
 {
@@ -1070,68 +1052,66 @@ inline int lanes_per_site(int nslot)
     return r;
 }
 
-// Chunk shape of the walk: cy rows x cz planes of full x rows with cy | Ly,
-// cz | Lz, a multiple of 64 sites up to maxcs, each 64 threads one aligned
-// 64-site tile (cy = Ly, or cy * Lx/2 a multiple of 64); the fewest halo
-// neighbours per site (2/cy + 2/cz, no term for a dimension the chunk spans),
-// then the largest chunk.  False if no shape fits.
-inline bool walk_chunk(const Geom &g, int maxcs, int &cy, int &cz)
+// Timeslices walked per block, a divisor of Lt up to 8 (TM_LDS_TWALK).  A block
+// that walks tw timeslices takes tw + 1 steps (its first loads stage two
+// timeslices), and the chip runs 256 CUs x 4 SIMDs x waves at a time, so the
+// walk is the longest that does not lengthen rounds x (tw + 1).  Long walks
+// pay on large launches (12 FP32 right-hand sides at 32^3x64, both parities:
+// 8 / 4 / 2 / 1 timeslices 1688 / 1728 / 1878 / 2225 us); on small ones they
+// leave CUs idle (one FP64 M at 16^3x32: 148 / 78 / 45 / 32 us; 12 FP32
+// right-hand sides: 117 / 87 / 91 / 102 us).  The outputs have the same bits.
+inline int walk_length(const Geom &g, const WalkPlan &p, int nslot, int waves)
 {
+    static const int most = std::max(1, env_knob("TM_LDS_TWALK", 8));
+    const double cap = 1024.0 * waves / (p.threads / 64);
     double best = 1e30;
-    int bs = 0;
-    for (int y = 1; y <= g.L[1]; y++) {
-        if (g.L[1] % y) continue;
-        for (int z = 1; z <= g.L[2]; z++) {
-            if (g.L[2] % z) continue;
-            const int cs = y * z * g.lxh;
-            if (cs > maxcs || cs % 64) continue;
-            if (y != g.L[1] && (y * g.lxh) % 64) continue;
-            const double halo = (y < g.L[1] ? 2.0 / y : 0.0) + (z < g.L[2] ? 2.0 / z : 0.0);
-            if (halo < best - 1e-12 || (halo < best + 1e-12 && cs > bs)) {
-                best = halo;
-                bs = cs;
-                cy = y;
-                cz = z;
-            }
+    int len = 1;
+    for (int tw = std::min(most, g.L[3]); tw >= 1; tw--) {
+        if (g.L[3] % tw) continue;
+        double rounds = (double)p.chunks * (g.L[3] / tw) * nslot / cap;
+        if (rounds <= 4.0) rounds = std::ceil(rounds);
+        const double cost = rounds * (tw + 1);
+        if (cost < best - 1e-9) {
+            best = cost;
+            len = tw;
         }
     }
-    return bs > 0;
-}
-
-// timeslices per block of the LDS walk (TM_LDS_TWALK; TM_LDS_WALK=0 disables the walk)
-inline int lds_twalk()
-{
-    static const int tw = env_knob("TM_LDS_WALK", 1) ? std::max(1, env_knob("TM_LDS_TWALK", 8)) : 0;
-    return tw;
+    return len;
 }
 
 template <int SP, bool DAG, int EPI, bool IN2, int SRC = 0, int PO = SP>
 static bool launch_walk(DslashArgs A, hipStream_t s)
 {
     {
-        int tw = lds_twalk();
         const uint64_t field = (uint64_t)A.g.vh * (SP == P64 ? 192 : SP == P32 ? 96 : 52);
-        if (tw < 1 || field >= (1ull << 32) || !walk_chunk(A.g, walk_max<SP>(), A.wcy, A.wcz)) return false;
-        while (A.g.L[3] % tw) tw--;
+        const WalkPlan plan = walk_plan(A.g);
+        if (!plan.tiles || field >= (1ull << 32)) return false;
+        A.wcy = plan.cy;
+        A.wcz = plan.cz;
+        const int tw = walk_length(A.g, plan, A.nslot, walk_waves<SP, EPI>());
         A.twalk = tw;
         A.in_span = (uint32_t)field;
         A.gauge_span = (uint32_t)std::min<uint64_t>(
             (uint64_t)2 * 4 * A.g.vh * (SP == P64 ? 96 : SP == P32 ? 48 : HALF_LINK_BYTES), 0xFFFFFFFFull);
         static const int gouter = env_knob("TM_GROUP_OUTER", 0);
         A.gouter = gouter;
-        const int cs = A.wcy * A.wcz * A.g.lxh;
-        A.nblk_site = (A.g.v3h / cs) * (A.g.L[3] / tw);
-        A.ntile = ntile_of(A.g);
+        A.nblk_site = plan.chunks * (A.g.L[3] / tw);
+        A.ntile = plan.tiles;
         const int total = A.nblk_site * A.nslot;
         const int grid = A.swz ? 8 * ((total + 7) / 8) : total;
+        const bool part = plan.cy * plan.cz * A.g.lxh != plan.threads;
         // outputs are streamed past L2 (non-temporal), keeping it for the halo lines
-        if constexpr (SRC != 0 || PO != SP)
-            hipLaunchKernelGGL((k_dslash_walk<SP, DAG, EPI, IN2, false, true, SRC, PO>), dim3(grid), dim3(cs), 0, s,
-                               A);
-        else if (A.st)
-            hipLaunchKernelGGL((k_dslash_walk<SP, DAG, EPI, IN2, true, true>), dim3(grid), dim3(cs), 0, s, A);
-        else
-            hipLaunchKernelGGL((k_dslash_walk<SP, DAG, EPI, IN2, false, true>), dim3(grid), dim3(cs), 0, s, A);
+        auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(plan.threads), 0, s, A); };
+        if constexpr (SRC != 0 || PO != SP) {
+            if (part) go(k_dslash_walk<SP, DAG, EPI, IN2, false, true, SRC, PO, true>);
+            else go(k_dslash_walk<SP, DAG, EPI, IN2, false, true, SRC, PO>);
+        } else if (A.st) {
+            if (part) go(k_dslash_walk<SP, DAG, EPI, IN2, true, true, 0, SP, true>);
+            else go(k_dslash_walk<SP, DAG, EPI, IN2, true, true>);
+        } else {
+            if (part) go(k_dslash_walk<SP, DAG, EPI, IN2, false, true, 0, SP, true>);
+            else go(k_dslash_walk<SP, DAG, EPI, IN2, false, true>);
+        }
         return true;
     }
 }

@@ -3,9 +3,64 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+#include <cstdlib>
+
 #include "tm_types.h"
 
 namespace tmk {
+
+// integer tuning knob from the environment (read once by its callers)
+inline int env_knob(const char *name, int dflt)
+{
+    const char *e = getenv(name);
+    return e ? atoi(e) : dflt;
+}
+
+// Chunk of the timeslice walk: cy rows (y) x cz planes (z) of full x rows with
+// cy | Ly, cz | Lz, one site per thread; the block has whole waves, the lanes
+// beyond the last site idle.  tiles: reduction tiles (one per wave) of a
+// half field, 0 if no chunk fits (a row longer than a block) or the walk is
+// switched off (TM_LDS_WALK=0).
+constexpr int WALK_MAX = 256;  // threads per block
+struct WalkPlan {
+    int cy = 0, cz = 0, threads = 0, chunks = 0, tiles = 0;
+};
+// The shape with the least modelled time per site: 1 + 0.09 per halo
+// neighbour (2/cy + 2/cz, no term for a dimension the chunk spans), over the
+// share of busy lanes; among equals the largest.  The 0.09 is the measured
+// slope (FP32, 12 right-hand sides, 32^3x64: 840 us at 1.0 halo neighbours per
+// site, 876 us at 1.5); idle lanes cost their issue slots.  It depends on the
+// lattice alone, so a slot's reduction tiles are the same in every batch.
+inline WalkPlan walk_plan(const Geom &g)
+{
+    static const bool on = env_knob("TM_LDS_WALK", 1) != 0;
+    WalkPlan p;
+    if (!on) return p;
+    double best = 1e30;
+    int sites = 0;
+    for (int y = 1; y <= g.L[1]; y++) {
+        if (g.L[1] % y) continue;
+        for (int z = 1; z <= g.L[2]; z++) {
+            const int cs = y * z * g.lxh;
+            if (g.L[2] % z || cs > WALK_MAX) continue;
+            const int threads = (cs + 63) & ~63;
+            const double halo = (y < g.L[1] ? 2.0 / y : 0.0) + (z < g.L[2] ? 2.0 / z : 0.0);
+            const double cost = (1.0 + 0.09 * halo) * threads / cs;
+            if (cost < best - 1e-9 || (cost < best + 1e-9 && cs > sites)) {
+                best = cost;
+                sites = cs;
+                p.cy = y;
+                p.cz = z;
+                p.threads = threads;
+            }
+        }
+    }
+    if (!sites) return p;
+    p.chunks = (g.L[1] / p.cy) * (g.L[2] / p.cz);
+    p.tiles = p.chunks * (p.threads / 64) * g.L[3];
+    return p;
+}
 
 // Dslash with epilogue; sp = storage precision of in/in2/out/p and of x, r
 // in the CG update (links of the same precision).  Returns -1 on an
@@ -148,7 +203,12 @@ inline size_t link_array_bytes(int p, const Geom &g)
     return (size_t)2 * 4 * g.vh * (p == P64 ? 96 : p == P32 ? 48 : HALF_LINK_BYTES);
 }
 __host__ __device__ inline int nblk_of(const Geom &g) { return (g.vh + BLOCK - 1) / BLOCK; }
-// per-slot partial sums: one per 64-site tile
-__host__ __device__ inline int ntile_of(const Geom &g) { return (g.vh + TILE - 1) / TILE; }
+// per-slot partial sums: one per wave of the timeslice walk, or per 64-site
+// tile where no chunk fits
+inline int ntile_of(const Geom &g)
+{
+    const WalkPlan p = walk_plan(g);
+    return p.tiles ? p.tiles : (g.vh + TILE - 1) / TILE;
+}
 
 }  // namespace tmk

@@ -135,7 +135,7 @@ struct DslashArgs {
     double kappa_u, a_u;  // used when st == nullptr
     SlotState *st;
     int nslot, nblk_site, swz;  // nblk_site: blocks over the sites (set by the launcher)
-    int ntile;                  // 64-site reduction tiles per slot
+    int ntile;                  // reduction tiles per slot (one per wave of the walk, or per 64 sites)
     uint32_t in_span, gauge_span;  // bytes reachable through the buffer resources (set by the launcher)
     int twalk;                     // timeslices walked per block (set by the launcher)
     int gouter;                    // slot groups slowest in the block order (set by the launcher)
