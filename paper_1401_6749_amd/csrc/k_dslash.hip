@@ -288,15 +288,14 @@ __device__ __forceinline__ void raw_setup(RawZ4<T> &z, double den, double a)
 }
 
 // ---------------------------------------------------------------------------
-// FP16 hop with FP32 arithmetic on the stored halves.  A stored spinor
-// component and a stored link entry are each one 32-bit word holding a
+// Half-precision hop with FP32 arithmetic on the stored halves.  A stored
+// spinor component and a stored link entry are each one 32-bit word holding a
 // complex number as two halves (re low, im high).  Every operation is an FP32
-// fused multiply-add whose FP16 operands are widened exactly inside the
-// instruction (v_fma_mix_f32), so neither the neighbour spinor nor the link
-// is decoded into registers first: the spin projection is one FP32 add per
-// real component and the colour transport four FP32 multiply-adds per complex
-// product, the same arithmetic as the FP32 kernel.  The neighbour's per-site
-// scale enters in the FP32 accumulation.
+// fused multiply-add, written out so that every kernel rounds alike.  FP16
+// operands are widened exactly inside the instruction (v_fma_mix_f32), so
+// neither the neighbour spinor nor the link is decoded into registers first
+// (BF16 ones by a shift or a mask).  The neighbour's per-site scale enters the
+// spin projection.
 // ---------------------------------------------------------------------------
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 
@@ -306,10 +305,18 @@ __device__ __forceinline__ h2 as_h2(uint32_t x)
     __builtin_memcpy(&r, &x, 4);
     return r;
 }
-__device__ __forceinline__ float lo_f(uint32_t x) { return (float)as_h2(x).x; }
-__device__ __forceinline__ float hi_f(uint32_t x) { return (float)as_h2(x).y; }
+template <int P>
+__device__ __forceinline__ float lo_f(uint32_t x)
+{
+    return P == P16 ? (float)as_h2(x).x : __uint_as_float(x << 16);
+}
+template <int P>
+__device__ __forceinline__ float hi_f(uint32_t x)
+{
+    return P == P16 ? (float)as_h2(x).y : __uint_as_float(x & 0xFFFF0000u);
+}
 
-// FP16 link (par, mu) of site i for the packed-operand transport: the
+// Half-precision link (par, mu) of site i for the packed-operand transport: the
 // stored entries as packed complex halves (re low, im high), all nine or,
 // with TM_HALF_LINK12, rows 0 and 1 with row 2 rebuilt in FP32 as the
 // conjugated cross product of the two
@@ -318,16 +325,18 @@ struct LinkPk {
     float r2[TM_HALF_LINK12 ? 6 : 1];
 };
 // entry (row, col) of a packed link as FP32 (re, im)
+template <int P>
 __device__ __forceinline__ void link_entry(const LinkPk &L, int row, int col, float &re, float &im)
 {
     if (TM_HALF_LINK12 != 0 && row == 2) {
         re = L.r2[2 * col];
         im = L.r2[2 * col + 1];
     } else {
-        re = lo_f(L.w[3 * row + col]);
-        im = hi_f(L.w[3 * row + col]);
+        re = lo_f<P>(L.w[3 * row + col]);
+        im = hi_f<P>(L.w[3 * row + col]);
     }
 }
+template <int P>
 __device__ __forceinline__ void load_link_words(__amdgpu_buffer_rsrc_t rs, int vh, int par, int mu, int i, LinkPk &L)
 {
     const uint32_t base = (uint32_t)(par * 4 + mu) * (uint32_t)HALF_LINK_BYTES * (uint32_t)vh;
@@ -342,8 +351,8 @@ __device__ __forceinline__ void load_link_words(__amdgpu_buffer_rsrc_t rs, int v
 #pragma unroll
         for (int j = 0; j < 3; j++) {
             const int k = (j + 1) % 3, l = (j + 2) % 3;
-            const float ar = lo_f(L.w[k]), ai = hi_f(L.w[k]), br = lo_f(L.w[3 + l]), bi = hi_f(L.w[3 + l]);
-            const float cr = lo_f(L.w[l]), ci = hi_f(L.w[l]), dr = lo_f(L.w[3 + k]), di = hi_f(L.w[3 + k]);
+            const float ar = lo_f<P>(L.w[k]), ai = hi_f<P>(L.w[k]), br = lo_f<P>(L.w[3 + l]), bi = hi_f<P>(L.w[3 + l]);
+            const float cr = lo_f<P>(L.w[l]), ci = hi_f<P>(L.w[l]), dr = lo_f<P>(L.w[3 + k]), di = hi_f<P>(L.w[3 + k]);
             // a b - c d, then conjugated
             L.r2[2 * j] = fmaf(ar, br, fmaf(-ai, bi, fmaf(-cr, dr, ci * di)));
             L.r2[2 * j + 1] = -fmaf(ar, bi, fmaf(ai, br, fmaf(-cr, di, -(ci * dr))));
@@ -359,28 +368,28 @@ __device__ __forceinline__ void load_link_words(__amdgpu_buffer_rsrc_t rs, int v
 // sc times the half spinor of colour c for the projector (1 + S g_mu), FP32,
 // from the stored words p[3*spin + colour]: two mixed-precision FMAs per real
 // component, so the neighbour's scale costs nothing later
-template <int MU, int S>
+template <int P, int MU, int S>
 __device__ __forceinline__ void project_pk(const uint32_t p[12], int c, float sc, cpx<float> &h0, cpx<float> &h1)
 {
     const uint32_t p0 = p[c], p1 = p[3 + c], p2 = p[6 + c], p3 = p[9 + c];
     const float s = S > 0 ? sc : -sc;
     if (MU == 0) {  // p0 - i S p3, p1 - i S p2
-        h0 = {fmaf(sc, lo_f(p0), fmaf(s, hi_f(p3), 0.f)), fmaf(sc, hi_f(p0), fmaf(-s, lo_f(p3), 0.f))};
-        h1 = {fmaf(sc, lo_f(p1), fmaf(s, hi_f(p2), 0.f)), fmaf(sc, hi_f(p1), fmaf(-s, lo_f(p2), 0.f))};
+        h0 = {fmaf(sc, lo_f<P>(p0), fmaf(s, hi_f<P>(p3), 0.f)), fmaf(sc, hi_f<P>(p0), fmaf(-s, lo_f<P>(p3), 0.f))};
+        h1 = {fmaf(sc, lo_f<P>(p1), fmaf(s, hi_f<P>(p2), 0.f)), fmaf(sc, hi_f<P>(p1), fmaf(-s, lo_f<P>(p2), 0.f))};
     } else if (MU == 1) {  // p0 - S p3, p1 + S p2
-        h0 = {fmaf(sc, lo_f(p0), fmaf(-s, lo_f(p3), 0.f)), fmaf(sc, hi_f(p0), fmaf(-s, hi_f(p3), 0.f))};
-        h1 = {fmaf(sc, lo_f(p1), fmaf(s, lo_f(p2), 0.f)), fmaf(sc, hi_f(p1), fmaf(s, hi_f(p2), 0.f))};
+        h0 = {fmaf(sc, lo_f<P>(p0), fmaf(-s, lo_f<P>(p3), 0.f)), fmaf(sc, hi_f<P>(p0), fmaf(-s, hi_f<P>(p3), 0.f))};
+        h1 = {fmaf(sc, lo_f<P>(p1), fmaf(s, lo_f<P>(p2), 0.f)), fmaf(sc, hi_f<P>(p1), fmaf(s, hi_f<P>(p2), 0.f))};
     } else if (MU == 2) {  // p0 - i S p2, p1 + i S p3
-        h0 = {fmaf(sc, lo_f(p0), fmaf(s, hi_f(p2), 0.f)), fmaf(sc, hi_f(p0), fmaf(-s, lo_f(p2), 0.f))};
-        h1 = {fmaf(sc, lo_f(p1), fmaf(-s, hi_f(p3), 0.f)), fmaf(sc, hi_f(p1), fmaf(s, lo_f(p3), 0.f))};
+        h0 = {fmaf(sc, lo_f<P>(p0), fmaf(s, hi_f<P>(p2), 0.f)), fmaf(sc, hi_f<P>(p0), fmaf(-s, lo_f<P>(p2), 0.f))};
+        h1 = {fmaf(sc, lo_f<P>(p1), fmaf(-s, hi_f<P>(p3), 0.f)), fmaf(sc, hi_f<P>(p1), fmaf(s, lo_f<P>(p3), 0.f))};
     } else {  // p0 + S p2, p1 + S p3
-        h0 = {fmaf(sc, lo_f(p0), fmaf(s, lo_f(p2), 0.f)), fmaf(sc, hi_f(p0), fmaf(s, hi_f(p2), 0.f))};
-        h1 = {fmaf(sc, lo_f(p1), fmaf(s, lo_f(p3), 0.f)), fmaf(sc, hi_f(p1), fmaf(s, hi_f(p3), 0.f))};
+        h0 = {fmaf(sc, lo_f<P>(p0), fmaf(s, lo_f<P>(p2), 0.f)), fmaf(sc, hi_f<P>(p0), fmaf(s, hi_f<P>(p2), 0.f))};
+        h1 = {fmaf(sc, lo_f<P>(p1), fmaf(s, lo_f<P>(p3), 0.f)), fmaf(sc, hi_f<P>(p1), fmaf(s, hi_f<P>(p3), 0.f))};
     }
 }
 
 // w = U h (FWD) or U^dagger h from the link entries
-template <bool FWD>
+template <int P, bool FWD>
 __device__ __forceinline__ void transport_pk(const LinkPk &u, const cpx<float> h[3], float wr[3], float wi[3])
 {
 #pragma unroll
@@ -389,7 +398,7 @@ __device__ __forceinline__ void transport_pk(const LinkPk &u, const cpx<float> h
 #pragma unroll
         for (int b = 0; b < 3; b++) {
             float ur, ui;
-            link_entry(u, FWD ? a : b, FWD ? b : a, ur, ui);
+            link_entry<P>(u, FWD ? a : b, FWD ? b : a, ur, ui);
             if (!FWD) ui = -ui;
             re = fmaf(ur, h[b].re, fmaf(-ui, h[b].im, re));
             im = fmaf(ur, h[b].im, fmaf(ui, h[b].re, im));
@@ -399,11 +408,11 @@ __device__ __forceinline__ void transport_pk(const LinkPk &u, const cpx<float> h
     }
 }
 
-// hop_w of one FP16 neighbour n of site s on packed operands (see above); raw
+// hop_w of one half-precision neighbour n of site s on packed operands (see above); raw
 // holds the neighbour's stored words.
-template <int MU, bool FWD, bool DAG>
+template <int P, int MU, bool FWD, bool DAG>
 __device__ __forceinline__ void hop_w_pk(const DslashArgs &A, __amdgpu_buffer_rsrc_t gauge, const Site &s, int n,
-                                         const RawHalf<P16, float> &raw, cpx<float> w[6])
+                                         const RawHalf<P, float> &raw, cpx<float> w[6])
 {
     const int vh = A.g.vh;
     constexpr int S = (FWD != DAG) ? -1 : 1;
@@ -412,16 +421,16 @@ __device__ __forceinline__ void hop_w_pk(const DslashArgs &A, __amdgpu_buffer_rs
     for (int k = 0; k < 12; k++) p[k] = raw.q[k >> 2][k & 3];
     float sc = raw.sc;
     LinkPk u;
-    load_link_words(gauge, vh, FWD ? A.out_par : 1 - A.out_par, MU, FWD ? s.cb : n, u);
+    load_link_words<P>(gauge, vh, FWD ? A.out_par : 1 - A.out_par, MU, FWD ? s.cb : n, u);
     if (MU == 3 && A.g.tbc < 0 && s.t == (FWD ? A.g.L[3] - 1 : 0)) sc = -sc;
     cpx<float> h0[3], h1[3];
 #pragma unroll
-    for (int c = 0; c < 3; c++) project_pk<MU, S>(p, c, sc, h0[c], h1[c]);
+    for (int c = 0; c < 3; c++) project_pk<P, MU, S>(p, c, sc, h0[c], h1[c]);
     float wr[3], wi[3];
-    transport_pk<FWD>(u, h0, wr, wi);
+    transport_pk<P, FWD>(u, h0, wr, wi);
 #pragma unroll
     for (int a = 0; a < 3; a++) w[a] = cpx<float>{wr[a], wi[a]};
-    transport_pk<FWD>(u, h1, wr, wi);
+    transport_pk<P, FWD>(u, h1, wr, wi);
 #pragma unroll
     for (int a = 0; a < 3; a++) w[3 + a] = cpx<float>{wr[a], wi[a]};
 }
@@ -433,8 +442,8 @@ template <class T, int SP, int MU, bool FWD, bool DAG, class RawT>
 __device__ __forceinline__ void hop_w(const DslashArgs &A, __amdgpu_buffer_rsrc_t gauge, const Site &s, int n,
                                       const RawT &raw, cpx<T> w[6])
 {
-    if constexpr (SP == P16 && std::is_same<RawT, RawHalf<P16, float>>::value) {
-        hop_w_pk<MU, FWD, DAG>(A, gauge, s, n, raw, w);
+    if constexpr (std::is_same<RawT, RawHalf<SP, float>>::value) {
+        hop_w_pk<SP, MU, FWD, DAG>(A, gauge, s, n, raw, w);
         return;
     }
     constexpr int S = (FWD != DAG) ? -1 : 1;
@@ -1021,6 +1030,112 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
     }
 }
 
+// ---------------------------------------------------------------------------
+// Small launches: one wave per neighbour direction.
+//
+// Where the sites of a launch leave most SIMDs without a wave, a hop's time is
+// the chain of its memory latencies: two timeslices staged, a barrier, and the
+// eight neighbours' links and halo spinors one after another.  Here a block of
+// eight waves computes the sites of one reduction tile (one wave of a walk
+// chunk, the same sites in the same lanes) for one right-hand side: wave d
+// loads neighbour d and its link and transports it, so the eight latencies
+// overlap; the half spinors meet in LDS and wave 0 adds them in the walk's
+// order (backward t, x, y, z, forward t) and runs the epilogue.  Outputs and
+// sums have the walk's bits.
+// ---------------------------------------------------------------------------
+template <class T, int SP, int MU, bool FWD, bool DAG, class RawT>
+__device__ __forceinline__ void split_dir(const DslashArgs &A, const HopRes &R, const Site &s, double den, double a,
+                                          cpx<T> w[6])
+{
+    const int n = nbr<MU, FWD ? 1 : -1>(A.g, s);
+    RawT raw;
+    raw_setup(raw, den, a);
+    raw.load(R.in, 0, A.g.vh, n);
+    hop_w<T, SP, MU, FWD, DAG, RawT>(A, R.gauge, s, n, raw, w);
+}
+
+template <int SP, bool DAG, int EPI, bool IN2, bool SLOT, int SRC = 0, int PO = SP>
+__global__ __launch_bounds__(512, (SP == P64 ? 2 : 4)) void k_dslash_split(const DslashArgs A)
+{
+    using T = typename Real<SP>::T;
+    __shared__ cpx<T> half[8][6][64];
+    int tile, slot;
+    if (!map_block(A.nblk_site, A.nslot, A.swz, tile, slot)) return;
+    double kappa = A.kappa_u, a = A.a_u, alpha = 0;
+    if constexpr (SLOT) {
+        const SlotState &st = A.st[slot];
+        if (st.status != ST_RUNNING) return;  // uniform over the block
+        kappa = st.kappa;
+        a = st.a;
+        alpha = st.alpha;
+    }
+    const Geom &g = A.g;
+    const int lane = (int)threadIdx.x & 63, d = (int)threadIdx.x >> 6;
+    // tile = (timeslice, chunk, wave of the chunk)
+    const int ncy = g.L[1] / A.wcy, chunks = ncy * (g.L[2] / A.wcz);
+    const int cs = A.wcy * A.wcz * g.lxh, wpc = (cs + 63) >> 6;
+    const int tc = tile / wpc, t = tc / chunks, c = tc - t * chunks;
+    const int lw = (tile - tc * wpc) * 64 + lane;
+    const bool live = lw < cs;
+    const int l = live ? lw : cs - 1;
+    const int rz = l / g.lxh, xh = l - rz * g.lxh;
+    const int yy = rz % A.wcy, zz = rz / A.wcy;
+    const int cb = t * g.st + xh + g.sy * ((c % ncy) * A.wcy + yy) + g.sz * ((c / ncy) * A.wcz + zz);
+    const Site s = site_of(g, cb, A.out_par);
+    HopRes R;
+    R.gauge = mkrsrc(A.gauge, A.gauge_span);
+    R.lane = 0;
+    double den = 0.0;
+    if constexpr (SRC & 1) {
+        R.in = mkrsrc(A.codes + (size_t)slot * A.codes_slot / 4 + (size_t)(1 - A.out_par) * g.vh, (uint32_t)g.vh * 4u);
+        den = 1.0 / (1.0 + a * a);
+    } else {
+        R.in = mkrsrc(A.in + (size_t)slot * A.in_slot, A.in_span);
+    }
+    using RawT = typename std::conditional<(SRC & 1) != 0, RawZ4<T>, typename RawSel<SP, T>::type>::type;
+    cpx<T> w[6];
+    switch (__builtin_amdgcn_readfirstlane(d)) {
+    case 0: split_dir<T, SP, 3, false, DAG, RawT>(A, R, s, den, a, w); break;
+    case 1: split_dir<T, SP, 0, true, DAG, RawT>(A, R, s, den, a, w); break;
+    case 2: split_dir<T, SP, 0, false, DAG, RawT>(A, R, s, den, a, w); break;
+    case 3: split_dir<T, SP, 1, true, DAG, RawT>(A, R, s, den, a, w); break;
+    case 4: split_dir<T, SP, 1, false, DAG, RawT>(A, R, s, den, a, w); break;
+    case 5: split_dir<T, SP, 2, true, DAG, RawT>(A, R, s, den, a, w); break;
+    case 6: split_dir<T, SP, 2, false, DAG, RawT>(A, R, s, den, a, w); break;
+    default: split_dir<T, SP, 3, true, DAG, RawT>(A, R, s, den, a, w); break;
+    }
+#pragma unroll
+    for (int k = 0; k < 6; k++) half[d][k][lane] = w[k];
+    __syncthreads();
+    if (d != 0) return;
+    constexpr int SF = DAG ? 1 : -1;  // projector sign of a forward neighbour
+    cpx<T> acc[12];
+#pragma unroll
+    for (int k = 0; k < 12; k++) acc[k] = cpx<T>{(T)0, (T)0};
+    auto add = [&](int e, auto mu, auto sign) {
+        cpx<T> v[6];
+#pragma unroll
+        for (int k = 0; k < 6; k++) v[k] = half[e][k][lane];
+        accum<T, decltype(mu)::value, decltype(sign)::value>(acc, v);
+    };
+    using P = std::integral_constant<int, SF>;
+    using M = std::integral_constant<int, -SF>;
+    add(0, std::integral_constant<int, 3>{}, M{});
+    add(1, std::integral_constant<int, 0>{}, P{});
+    add(2, std::integral_constant<int, 0>{}, M{});
+    add(3, std::integral_constant<int, 1>{}, P{});
+    add(4, std::integral_constant<int, 1>{}, M{});
+    add(5, std::integral_constant<int, 2>{}, P{});
+    add(6, std::integral_constant<int, 2>{}, M{});
+    add(7, std::integral_constant<int, 3>{}, P{});
+    double part = 0.0;
+    if (live) part = epilogue<SP, EPI, IN2, SRC, false, PO>(A, slot, cb, acc, kappa, a, alpha);
+    if constexpr (EPI != EPI_PLAIN) {
+        const double v = wave_sum(part);
+        if (lane == 0) A.partial[(size_t)slot * A.ntile + tile] = v;
+    }
+}
+
 template <int SP, bool DAG, int EPI, bool IN2, int R>
 static void launch_r(const DslashArgs &A, hipStream_t s)
 {
@@ -1079,6 +1194,13 @@ inline int walk_length(const Geom &g, const WalkPlan &p, int nslot, int waves)
     return len;
 }
 
+// Most reduction tiles x right-hand sides of a launch on k_dslash_split: one
+// block per CU.  Both parities of a hop: 64 tiles (8^3x16, one FP64 right-hand
+// side) 10.7 us against the walk's 17.4 us; 768 tiles (12 of them) 26.4
+// against 21.5 us, as each block then reads its neighbours from L2 where the
+// walk has them in LDS.
+constexpr int SPLIT_MOST = 256;
+
 template <int SP, bool DAG, int EPI, bool IN2, int SRC = 0, int PO = SP>
 static bool launch_walk(DslashArgs A, hipStream_t s)
 {
@@ -1088,6 +1210,15 @@ static bool launch_walk(DslashArgs A, hipStream_t s)
         if (!plan.tiles || field >= (1ull << 32)) return false;
         A.wcy = plan.cy;
         A.wcz = plan.cz;
+        if (plan.tiles * A.nslot <= SPLIT_MOST) {
+            A.in_span = (uint32_t)field;
+            A.gauge_span = (uint32_t)std::min<uint64_t>((uint64_t)2 * 4 * A.g.vh * link_bytes(SP), 0xFFFFFFFFull);
+            A.nblk_site = A.ntile = plan.tiles;
+            const int total = plan.tiles * A.nslot, grid = A.swz ? 8 * ((total + 7) / 8) : total;
+            if (A.st) hipLaunchKernelGGL((k_dslash_split<SP, DAG, EPI, IN2, PO == SP && SRC == 0, SRC, PO>), dim3(grid), dim3(512), 0, s, A);
+            else hipLaunchKernelGGL((k_dslash_split<SP, DAG, EPI, IN2, false, SRC, PO>), dim3(grid), dim3(512), 0, s, A);
+            return true;
+        }
         const int tw = walk_length(A.g, plan, A.nslot, walk_waves<SP, EPI>());
         A.twalk = tw;
         A.in_span = (uint32_t)field;

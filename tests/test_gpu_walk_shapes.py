@@ -44,3 +44,17 @@ def test_walk_reductions_match_oracle(oracle, dims):
     _, st = tm.tm_cg_solve(GU.context(), g, 0.12, 0.01, tm.solver_params("f64", tol=1e-10), 1, b, x)
     assert st[0]["iters"] == it and st[0]["true_rel_resid"] < 1e-9
     assert GU.relerr(GU.from_dev(x[0]).reshape(want.shape), want) < 1e-11
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16", "bf16"])
+@pytest.mark.parametrize("dims", [(8, 8, 8, 8), (12, 10, 4, 6)])
+def test_split_equals_walk(prec, dims):
+    """One right-hand side (one wave per neighbour direction) and sixteen of
+    them (the walk: more tiles than one block per CU) give the same bits."""
+    U = inputs.gauge_field(dims, seed=5)
+    g = GU.load(dims, U)
+    psi = np.stack([inputs.random_spinor(dims, 40 + r) for r in range(16)])
+    for op in ("hop", "mhat_dag_mhat"):
+        many = GU.apply_op(g, op, 0.14, 0.02, prec, psi, dims)
+        for r in (0, 9):
+            assert np.array_equal(many[r], GU.apply_op(g, op, 0.14, 0.02, prec, psi[r:r + 1], dims)[0]), (op, r)
