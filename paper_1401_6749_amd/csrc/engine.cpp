@@ -221,36 +221,6 @@ static DslashArgs dargs(const Batch *b, int sp)
     return A;
 }
 
-// one FP64 single-slot Dslash with uniform (kappa, a)
-static void d64(const Batch *b, bool dag, int epi, int coef, int out_par, const char *in, const char *in2, char *out,
-                double kappa, double a, double *partial = nullptr, const char *bvec = nullptr)
-{
-    DslashArgs A = dargs(b, P64);
-    A.in = in;
-    A.in2 = in2;
-    A.out = out;
-    A.out_par = out_par;
-    A.coef = coef;
-    A.kappa_u = kappa;
-    A.a_u = a;
-    A.partial = partial;
-    A.b = bvec;
-    launch_dslash(P64, dag, epi, in2 != nullptr, A, b->stream);
-}
-
-// eta of a job into FA = [even | odd] (FP64)
-static void load_eta(Batch *b, int slot, Job *j)
-{
-    const Geom &g = b->G->g;
-    uint32_t *codes = b->codes + (size_t)slot * 2 * g.vh;
-    if (j->noise) {
-        launch_z4_field(g, codes, 0, 0.0, b->FA, b->stream);
-        launch_z4_field(g, codes + g.vh, 0, 0.0, b->FA + b->h64, b->stream);
-    } else {
-        launch_field_import(P64, g, 1, j->b_canon, b->FA, b->stream);
-    }
-}
-
 // Prep/reconstruction precision class of a job: P32 for LP noise solves
 // (their target is a 1e-2 residual: reconstruction and contraction in FP32,
 // the preparation in the solve's half precision, see fill_noise_run),
@@ -258,37 +228,6 @@ static void load_eta(Batch *b, int slot, Job *j)
 static int prep_prec(const Batch *b, const Job *j)
 {
     return (j->noise && !j->want_true && (b->kind == K_LP16 || b->kind == K_LPBF)) ? P32 : P64;
-}
-
-// Dslash with uniform (kappa, a) in precision pp on single fields
-static void dsl(const Batch *b, int pp, bool dag, int epi, int coef, int out_par, const char *in, const char *in2,
-                char *out, double kappa, double a, double *partial = nullptr)
-{
-    DslashArgs A = dargs(b, pp);
-    A.in = in;
-    A.in2 = in2;
-    A.out = out;
-    A.out_par = out_par;
-    A.coef = coef;
-    A.kappa_u = kappa;
-    A.a_u = a;
-    A.partial = partial;
-    launch_dslash(pp, dag, epi, in2 != nullptr, A, b->stream);
-}
-
-// Dslash whose noise input comes from the slot's Z4 codes (src 3: prep, src 2: reconstruction)
-static void dsl_codes(const Batch *b, int pp, int src, int coef, int out_par, int slot, const char *in, char *out,
-                      double kappa, double a)
-{
-    DslashArgs A = dargs(b, pp);
-    A.codes = b->codes + (size_t)slot * 2 * b->G->g.vh;
-    A.in = in;
-    A.out = out;
-    A.out_par = out_par;
-    A.coef = coef;
-    A.kappa_u = kappa;
-    A.a_u = a;
-    launch_dslash_codes(pp, src, A, b->stream);
 }
 
 // Dslash with uniform (kappa, a) over n consecutive slots with the given pitches
@@ -342,6 +281,16 @@ static void job_start(Batch *b, int slot, Job *j)
     if (b->t_first == 0) b->t_first = j->t_fill;
 }
 
+static void start_params(SlotStartParams &P, int i, const Job *j)
+{
+    P.kappa[i] = j->kappa;
+    P.a[i] = j->a;
+    P.tol2[i] = j->fixed > 0 ? 0.0 : j->tol * j->tol;
+    P.max_iter[i] = j->fixed > 0 ? j->fixed : j->max_iter;
+    const double delta = j->delta > 0 ? j->delta : TM_DEFAULT_DELTA;
+    P.delta2[i] = delta * delta;
+}
+
 // Noise solves in the n consecutive slots from s0, equal (kappa, a) and
 // precision class pp (prep_prec), prepared together (FP64 for pp = P64,
 // else in the batch's half precision):
@@ -364,12 +313,7 @@ static void fill_noise_run(Batch *b, int s0, int n, Job *const *jobs, int pp)
         Z.src[i] = j->src;
         Z.tmod[i] = j->tmod;
         Z.tph[i] = j->tph;
-        P.kappa[i] = j->kappa;
-        P.a[i] = j->a;
-        P.tol2[i] = j->fixed > 0 ? 0.0 : j->tol * j->tol;
-        P.max_iter[i] = j->fixed > 0 ? j->fixed : j->max_iter;
-        const double delta = j->delta > 0 ? j->delta : TM_DEFAULT_DELTA;
-        P.delta2[i] = delta * delta;
+        start_params(P, i, j);
     }
     launch_z4_codes(g, Z, n, b->codes + (size_t)s0 * 2 * g.vh, s);
     // LP runs prepare their right-hand side in the solve's own half precision
@@ -377,7 +321,8 @@ static void fill_noise_run(Batch *b, int s0, int n, Job *const *jobs, int pp)
     const bool half = !mixed && pp == P32 && b->xr == b->sp && b->hxr == b->hsp && (b->xr == P16 || b->xr == PBF);
     const int pq = half ? b->sp : pp;
     const size_t w = n > 1 ? b->wpitch : half_bytes(pq, g);
-    char *Be = b->FB, *To = b->FC, *Ce = b->FA;
+    char *Be = b->FB, *To = b->FC, *Ce = mixed ? b->b64 + s0 * b->h64 : b->FA;
+    const size_t wc = mixed ? b->h64 : w;
     double *part = b->partial + (size_t)s0 * b->nblk;
     dsl_codes_run(b, pq, 3, CM_PREP, 0, s0, n, nullptr, 0, Be, w, kappa, a);
     dsl_run(b, pq, true, EPI_PLAIN, CM_AINV_DAG, 1, Be, w, nullptr, 0, To, w, kappa, a, n);
@@ -403,11 +348,11 @@ static void fill_noise_run(Batch *b, int s0, int n, Job *const *jobs, int pp)
         A.partial = part;
         fused = launch_dslash_start(pq, b->xr, A, s) == 0;
     }
-    if (!fused) dsl_run(b, pq, true, EPI_NORM, CM_MHAT_DAG, 0, To, w, Be, w, Ce, w, kappa, a, n, part);
+    if (!fused) dsl_run(b, pq, true, EPI_NORM, CM_MHAT_DAG, 0, To, w, Be, w, Ce, wc, kappa, a, n, part);
     launch_slot_start(b->st + s0, part, b->nblk, P, n, s);
     if (!fused) {
         if (b->xr == b->sp && b->hxr == b->hsp && (pq == P64 || pq == P32)) {
-            launch_cg_start(pq, b->xr, g, Ce, w, b->r + s0 * b->hxr, b->p + s0 * b->hsp, b->x + s0 * b->hxr, b->hxr,
+            launch_cg_start(pq, b->xr, g, Ce, wc, b->r + s0 * b->hxr, b->p + s0 * b->hsp, b->x + s0 * b->hxr, b->hxr,
                             n, s);
         } else {
             launch_convert(pq, b->xr, g, Ce, w, b->r + s0 * b->hxr, b->hxr, n, s);
@@ -415,10 +360,54 @@ static void fill_noise_run(Batch *b, int s0, int n, Job *const *jobs, int pp)
             launch_zero(b->xr, g, b->x + s0 * b->hxr, b->hxr, n, s);
         }
     }
-    if (mixed) {
-        launch_convert(P64, P64, g, Ce, w, b->b64 + s0 * b->h64, b->h64, n, s);
-        launch_zero(P64, g, b->x64 + s0 * b->h64, b->h64, n, s);
+    if (mixed) launch_zero(P64, g, b->x64 + s0 * b->h64, b->h64, n, s);
+}
+
+// Slots whose FP64 half fields one scratch array holds, pitch64 apart.
+static size_t pitch64(const Batch *b, int n) { return n > 1 ? slot_pitch(b->h64) : b->h64; }
+static int run_slots64(const Batch *b)
+{
+    return std::max(1, (int)std::min<size_t>(b->S, scratch_bytes(b->G->g, b->kind, b->S) / slot_pitch(b->h64)));
+}
+
+// Explicit sources in the n consecutive slots from s0 (n <= run_slots64, one
+// after another in the caller's canonical array, equal kappa and a),
+// prepared together in FP64:
+//   bhat_e = b_e + kappa D_eo A^-1 b_o,  rhs = Mhat^dag bhat.
+// Twelve slots in runs share the links of three Dslash launches instead of
+// reading them once each (12 FP16 solves at 24^3x48: see harvest_user_run).
+static void fill_user_run(Batch *b, int s0, int n, Job *const *jobs)
+{
+    const Geom &g = b->G->g;
+    hipStream_t s = b->stream;
+    const bool mixed = b->kind == K_MIXED;
+    const double kappa = jobs[0]->kappa, a = jobs[0]->a;
+    SlotStartParams P{};
+    P.mixed = mixed ? 1 : 0;
+    for (int i = 0; i < n; i++) {
+        job_start(b, s0 + i, jobs[i]);
+        start_params(P, i, jobs[i]);
     }
+    const size_t w = pitch64(b, n);
+    char *Be = b->FA, *To = b->FB, *Ce = mixed ? b->b64 + s0 * b->h64 : b->FC;
+    const size_t wc = mixed ? b->h64 : w;
+    double *part = b->partial + (size_t)s0 * b->nblk;
+    launch_eta_import(g, n, jobs[0]->b_canon, Be, To, w, true, a, s);
+    // bhat over b_e: each site reads its own b_e before it writes
+    dsl_run(b, P64, false, EPI_PLAIN, CM_PREP, 0, To, w, Be, w, Be, w, kappa, a, n);
+    dsl_run(b, P64, true, EPI_PLAIN, CM_AINV_DAG, 1, Be, w, nullptr, 0, To, w, kappa, a, n);
+    dsl_run(b, P64, true, EPI_NORM, CM_MHAT_DAG, 0, To, w, Be, w, Ce, wc, kappa, a, n, part);
+    launch_slot_start(b->st + s0, part, b->nblk, P, n, s);
+    launch_cg_start(P64, b->xr, g, Ce, wc, b->r + s0 * b->hxr, b->p + s0 * b->hsp, b->x + s0 * b->hxr, b->hxr, n, s);
+    if (mixed) launch_zero(P64, g, b->x64 + s0 * b->h64, b->h64, n, s);
+}
+
+// jobs that may share a run of explicit sources
+static bool next_user(const Batch *b, const Job *first, const Job *j, int i)
+{
+    const size_t site = (size_t)2 * b->G->g.vh * 24;
+    return !j->noise && j->kappa == first->kappa && j->a == first->a && j->b_canon == first->b_canon + i * site &&
+           j->x_canon == first->x_canon + i * site;
 }
 
 int batch_fill_many(Batch *b, Job *const *jobs, int njobs)
@@ -427,60 +416,26 @@ int batch_fill_many(Batch *b, Job *const *jobs, int njobs)
     for (int s = 0; s < b->S && (int)fs.size() < njobs; s++)
         if (!b->slot_job[s]) fs.push_back(s);
     const int m = (int)fs.size();
+    static const int cap_env = run_cap("TM_FILL_RUN");
     int k = 0;
     while (k < m) {
         Job *j = jobs[k];
-        if (!j->noise) {
-            batch_fill(b, fs[k], j);
-            k++;
-            continue;
-        }
-        const int pp = prep_prec(b, j);
-        static const int cap_env = run_cap("TM_FILL_RUN");
-        const int cap = pp == b->wpp ? std::min(b->wslots, cap_env) : 1;
         int n = 1;
-        while (k + n < m && n < cap && fs[k + n] == fs[k] + n && jobs[k + n]->noise &&
-               jobs[k + n]->kappa == j->kappa && jobs[k + n]->a == j->a && prep_prec(b, jobs[k + n]) == pp)
-            n++;
-        fill_noise_run(b, fs[k], n, jobs + k, pp);
+        if (!j->noise) {
+            const int cap = std::min(run_slots64(b), cap_env);
+            while (k + n < m && n < cap && fs[k + n] == fs[k] + n && next_user(b, j, jobs[k + n], n)) n++;
+            fill_user_run(b, fs[k], n, jobs + k);
+        } else {
+            const int pp = prep_prec(b, j);
+            const int cap = pp == b->wpp ? std::min(b->wslots, cap_env) : 1;
+            while (k + n < m && n < cap && fs[k + n] == fs[k] + n && jobs[k + n]->noise &&
+                   jobs[k + n]->kappa == j->kappa && jobs[k + n]->a == j->a && prep_prec(b, jobs[k + n]) == pp)
+                n++;
+            fill_noise_run(b, fs[k], n, jobs + k, pp);
+        }
         k += n;
     }
     return m;
-}
-
-int batch_fill(Batch *b, int slot, Job *j)
-{
-    if (j->noise) {
-        fill_noise_run(b, slot, 1, &j, prep_prec(b, j));
-        return TM_OK;
-    }
-    const Geom &g = b->G->g;
-    hipStream_t s = b->stream;
-    job_start(b, slot, j);
-    const bool mixed = b->kind == K_MIXED;
-    const double tol2 = j->fixed > 0 ? 0.0 : j->tol * j->tol;
-    const int maxit = j->fixed > 0 ? j->fixed : j->max_iter;
-    const double delta = j->delta > 0 ? j->delta : TM_DEFAULT_DELTA;
-    double *part = b->partial + (size_t)slot * b->nblk;
-    load_eta(b, slot, j);
-    char *Ee = b->FA, *Eo = b->FA + b->h64;
-    char *Be = b->FB, *Bo = b->FB + b->h64;
-    char *Ce = b->FC;
-    // bhat_e = eta_e + kappa D_eo A^-1 eta_o
-    launch_site_diag(g, 1, j->a, Eo, Bo, s);
-    d64(b, false, EPI_PLAIN, CM_PREP, 0, Bo, Ee, Be, j->kappa, j->a);
-    // rhs = Mhat^dag bhat = A^dag bhat - kappa^2 D'_eo A^-dag D'_oe bhat
-    d64(b, true, EPI_PLAIN, CM_AINV_DAG, 1, Be, nullptr, Bo, j->kappa, j->a);
-    d64(b, true, EPI_NORM, CM_MHAT_DAG, 0, Bo, Be, Ce, j->kappa, j->a, part);
-    launch_slot_start(b->st + slot, part, b->nblk, j->kappa, j->a, tol2, maxit, delta * delta, mixed ? 1 : 0, s);
-    launch_convert(P64, b->xr, g, Ce, 0, b->r + slot * b->hxr, 0, 1, s);
-    launch_convert(P64, b->sp, g, Ce, 0, b->p + slot * b->hsp, 0, 1, s);
-    launch_zero(b->xr, g, b->x + slot * b->hxr, 0, 1, s);
-    if (mixed) {
-        launch_convert(P64, P64, g, Ce, 0, b->b64 + slot * b->h64, 0, 1, s);
-        launch_zero(P64, g, b->x64 + slot * b->h64, 0, 1, s);
-    }
-    return TM_OK;
 }
 
 // One CG iteration for every running slot:
@@ -600,9 +555,6 @@ static void reliable_update_run(Batch *b, int s0, int n)
     for (int i = 0; i < n; i++) b->slot_updates[s0 + i]++;
 }
 
-static void harvest64(Batch *b, int slot, const SlotState &S, Job *j);
-static int true_residual(Batch *b, int slot, Job *j);
-
 // LP noise solves in the n consecutive slots from s0 (equal kappa, a):
 // s_e = x widened to FP32, s_o = A^-1 (eta_o + kappa D_oe s_e) from the codes,
 // contractions on FP32 s and FP32 links with FP64 sums.
@@ -651,8 +603,8 @@ static void harvest_lp_run(Batch *b, int s0, int n)
     }
 }
 
-// results of a finished slot: status, counts, optional true residual; frees the slot
-static int harvest_done(Batch *b, int slot, const SlotState &S)
+// results of a finished slot: status, counts; frees the slot
+static void harvest_done(Batch *b, int slot, const SlotState &S)
 {
     Job *j = b->slot_job[slot];
     j->iters = S.iter;
@@ -662,116 +614,132 @@ static int harvest_done(Batch *b, int slot, const SlotState &S)
     j->status = S.status == ST_CONVERGED ? TM_OK
                 : S.status == ST_MAXITER ? (j->fixed > 0 ? TM_OK : TM_ERR_NOCONV)
                                          : TM_ERR_NUMERIC;
-    if (j->want_true) {
-        int e = true_residual(b, slot, j);
-        if (e != TM_OK) return e;
-    }
     b->iters_done += S.iter;
     j->t_done = now_s();
     b->t_last = j->t_done;
     b->slot_job[slot] = nullptr;
-    return TM_OK;
 }
 
 // LP noise solves harvested in FP32 (their contraction needs a raw output)
 static bool lp_harvest(const Batch *b, const Job *j) { return prep_prec(b, j) == P32 && j->raw_out; }
 
-// reconstruct s = (s_e, s_o), contract or export, optional true residual
-static int harvest(Batch *b, int slot, const SlotState &S)
-{
-    Job *j = b->slot_job[slot];
-    if (lp_harvest(b, j)) harvest_lp_run(b, slot, 1);
-    else if (prep_prec(b, j) != P32) harvest64(b, slot, S, j);
-    return harvest_done(b, slot, S);
-}
-
-// FP64 reconstruction and contraction / export
-static void harvest64(Batch *b, int slot, const SlotState &S, Job *j)
+// FP64 solutions of a run: s_e where the solve left it (FP64 x, the mixed
+// solver's x64, or widened into FC), s_o in a scratch array at the same pitch.
+struct Sol64 {
+    char *se, *so;
+    size_t pitch;
+};
+static Sol64 sol64(Batch *b, int s0, int n)
 {
     const Geom &g = b->G->g;
-    hipStream_t s = b->stream;
-    // s_e (FP64) into FC even half
-    char *se = b->FC, *so = b->FC + b->h64;
-    if (b->kind == K_F64) {
-        launch_convert(P64, P64, g, b->x + slot * b->hxr, 0, se, 0, 1, s);
-    } else if (b->kind == K_MIXED) {
-        char *x64 = b->x64 + slot * b->h64;
-        if (S.status != ST_CONVERGED) launch_accum_x(g, x64, 0, b->x + slot * b->hxr, nullptr, 0, 1, s);
-        launch_convert(P64, P64, g, x64, 0, se, 0, 1, s);
-    } else {
-        launch_convert(b->xr, P64, g, b->x + slot * b->hxr, 0, se, 0, 1, s);
+    if (b->kind == K_F64) return {b->x + s0 * b->hxr, b->FC, b->hxr};
+    if (b->kind == K_MIXED) {
+        for (int i = s0; i < s0 + n; i++)
+            if (b->st_h[i].status != ST_CONVERGED)
+                launch_accum_x(g, b->x64 + i * b->h64, 0, b->x + i * b->hxr, nullptr, 0, 1, b->stream);
+        return {b->x64 + s0 * b->h64, b->FC, b->h64};
     }
-    char *Eo = b->FA + b->h64;
-    if (j->noise) {
-        // s_o = A^-1 (eta_o + kappa D_oe s_e) with eta_o from the codes
-        dsl_codes(b, P64, 2, CM_RECON, 1, slot, se, so, j->kappa, j->a);
-        if (j->raw_out && j->oet) {
-            // one-end trick (see harvest_lp_run), D_W s in FA = [even | odd]
-            char *re = b->FA, *ro = b->FA + b->h64;
-            d64(b, false, EPI_PLAIN, CM_M, 0, so, se, re, j->kappa, 0.0);
-            d64(b, false, EPI_PLAIN, CM_M, 1, se, so, ro, j->kappa, 0.0);
-            RawOuts R{}, R2{};
-            R.p[0] = j->raw_out;
-            R2.p[0] = j->raw_out2;
-            launch_contract_lr(P64, g, b->G->links[P64], se, so, 0, se, so, 0, b->cpart, R, 1, 0.0, -2.0 * j->a, s,
-                               j->local_only);
-            launch_contract_lr(P64, g, b->G->links[P64], re, ro, 0, se, so, 0, b->cpart, R2, 1, 2.0, 0.0, s,
-                               j->local_only);
-        } else if (j->raw_out) {
-            const uint32_t *codes = b->codes + (size_t)slot * 2 * g.vh;
-            if (j->local_only) {
-                RawOuts R{};
-                R.p[0] = j->raw_out;
-                launch_contract_local(P64, g, se, so, 0, codes, b->cpart, R, 1, s);
-            } else {
-                launch_contract(P64, g, b->G->links[P64], se, so, codes, b->cpart, j->raw_out, s);
-            }
-            if (j->hpe) {
-                // (BH)^4 s into FB = [even | odd] through FA (see harvest_lp_run)
-                char *ae = b->FA, *ao = b->FA + b->h64, *we = b->FB, *wo = b->FB + b->h64;
-                d64(b, false, EPI_PLAIN, CM_BH, 1, se, nullptr, ao, j->kappa, j->a);
-                d64(b, false, EPI_PLAIN, CM_BH, 0, ao, nullptr, we, j->kappa, j->a);
-                d64(b, false, EPI_PLAIN, CM_BH, 1, we, nullptr, ao, j->kappa, j->a);
-                d64(b, false, EPI_PLAIN, CM_BH, 0, ao, nullptr, we, j->kappa, j->a);
-                d64(b, false, EPI_PLAIN, CM_BH, 0, so, nullptr, ae, j->kappa, j->a);
-                d64(b, false, EPI_PLAIN, CM_BH, 1, ae, nullptr, wo, j->kappa, j->a);
-                d64(b, false, EPI_PLAIN, CM_BH, 0, wo, nullptr, ae, j->kappa, j->a);
-                d64(b, false, EPI_PLAIN, CM_BH, 1, ae, nullptr, wo, j->kappa, j->a);
-                RawOuts R2{};
-                R2.p[0] = j->raw_out2;
-                launch_contract_local(P64, g, we, wo, 0, codes, b->cpart, R2, 1, s);
-            }
-        }
-    } else {
-        load_eta(b, slot, j);
-        d64(b, false, EPI_PLAIN, CM_RECON, 1, se, Eo, so, j->kappa, j->a);
-        launch_field_export(P64, g, 1, b->FC, j->x_canon, s);
-    }
+    const size_t w = pitch64(b, n);
+    launch_convert(b->xr, P64, g, b->x + s0 * b->hxr, b->hxr, b->FC, w, n, b->stream);
+    return {b->FC, b->FD, w};
 }
 
-// |eta - M s| / |eta| in FP64 (s in FC, eta rebuilt in FA)
-static int true_residual(Batch *b, int slot, Job *j)
+// |eta - M s| / |eta| in FP64 of a run's solutions, eta's halves at Ee, Eo + i * w
+static int true_residual_run(Batch *b, int s0, int n, const Sol64 &s, const char *Ee, const char *Eo, size_t w)
 {
-    const Geom &g = b->G->g;
-    hipStream_t s = b->stream;
-    char *se = b->FC, *so = b->FC + b->h64;
-    load_eta(b, slot, j);
-    char *Ee = b->FA, *Eo = b->FA + b->h64;
-    char *Be = b->FB, *Bo = b->FB + b->h64;
-    double *p0 = b->partial + (size_t)slot * b->nblk;
+    const Job *j = b->slot_job[s0];
+    double *part = b->partial + (size_t)s0 * b->nblk;
+    auto sum = [&](int k) { launch_reduce(part, b->nblk, n, b->dres + k * MAX_SLOTS, b->stream); };
     // even: eta_e - (A s_e - kappa D_eo s_o); odd: eta_o - (A s_o - kappa D_oe s_e)
-    d64(b, false, EPI_RESID, CM_M, 0, so, se, Be, j->kappa, j->a, p0, Ee);
-    launch_reduce(p0, b->nblk, 1, b->dres + 0, s);
-    d64(b, false, EPI_RESID, CM_M, 1, se, so, Bo, j->kappa, j->a, p0, Eo);
-    launch_reduce(p0, b->nblk, 1, b->dres + 1, s);
-    launch_norm_partial(g, Ee, p0, s);
-    launch_reduce(p0, b->nblk, 1, b->dres + 2, s);
-    launch_norm_partial(g, Eo, p0, s);
-    launch_reduce(p0, b->nblk, 1, b->dres + 3, s);
-    TM_HIP(b->ctx, hipMemcpyAsync(b->hres, b->dres, 4 * sizeof(double), hipMemcpyDeviceToHost, s));
-    TM_HIP(b->ctx, hipStreamSynchronize(s));
-    const double num = b->hres[0] + b->hres[1], den = b->hres[2] + b->hres[3];
-    j->true_rel = den > 0 ? std::sqrt(num / den) : 0.0;
+    dsl_run(b, P64, false, EPI_RESID, CM_M, 0, s.so, s.pitch, s.se, s.pitch, nullptr, 0, j->kappa, j->a, n, part, Ee, w);
+    sum(0);
+    dsl_run(b, P64, false, EPI_RESID, CM_M, 1, s.se, s.pitch, s.so, s.pitch, nullptr, 0, j->kappa, j->a, n, part, Eo, w);
+    sum(1);
+    launch_norm_partial(b->G->g, Ee, w, n, part, b->stream);
+    sum(2);
+    launch_norm_partial(b->G->g, Eo, w, n, part, b->stream);
+    sum(3);
+    TM_HIP(b->ctx, hipMemcpyAsync(b->hres, b->dres, 4 * MAX_SLOTS * sizeof(double), hipMemcpyDeviceToHost, b->stream));
+    TM_HIP(b->ctx, hipStreamSynchronize(b->stream));
+    for (int i = 0; i < n; i++) {
+        const double *h = b->hres + i;
+        const double num = h[0] + h[MAX_SLOTS], den = h[2 * MAX_SLOTS] + h[3 * MAX_SLOTS];
+        b->slot_job[s0 + i]->true_rel = den > 0 ? std::sqrt(num / den) : 0.0;
+    }
+    return TM_OK;
+}
+
+// Explicit sources of the n consecutive slots from s0 (a run as in
+// fill_user_run): reconstruction, export and true residual in FP64.  In runs
+// the links are read once for all slots and the host waits once; slot by slot
+// twelve FP16 solves at 24^3x48 took 22.4 ms, 13 of them in the preparation
+// and here; in runs 16.8 ms.
+static int harvest_user_run(Batch *b, int s0, int n)
+{
+    const Geom &g = b->G->g;
+    const Job *j = b->slot_job[s0];
+    const size_t w = pitch64(b, n);
+    const Sol64 s = sol64(b, s0, n);
+    launch_eta_import(g, n, j->b_canon, b->FA, b->FB, w, false, 0.0, b->stream);
+    dsl_run(b, P64, false, EPI_PLAIN, CM_RECON, 1, s.se, s.pitch, b->FB, w, s.so, s.pitch, j->kappa, j->a, n);
+    launch_halves_export(g, n, s.se, s.pitch, s.so, s.pitch, j->x_canon, b->stream);
+    return j->want_true ? true_residual_run(b, s0, n, s, b->FA, b->FB, w) : TM_OK;
+}
+
+// Noise solves of the n consecutive slots from s0 with FP64 reconstruction
+// and contraction; the partial sums of a run go into its slots' own t fields.
+static int harvest64_run(Batch *b, int s0, int n)
+{
+    const Geom &g = b->G->g;
+    hipStream_t st = b->stream;
+    const Job *j = b->slot_job[s0];
+    const Sol64 s = sol64(b, s0, n);
+    const size_t w = s.pitch;
+    // s_o = A^-1 (eta_o + kappa D_oe s_e) with eta_o from the codes
+    dsl_codes_run(b, P64, 2, CM_RECON, 1, s0, n, s.se, w, s.so, w, j->kappa, j->a);
+    const uint32_t *codes = b->codes + (size_t)s0 * 2 * g.vh;
+    if (j->want_true) {  // n = 1
+        launch_z4_field(g, codes, 0, 0.0, b->FA, st);
+        launch_z4_field(g, codes + g.vh, 0, 0.0, b->FA + b->h64, st);
+        const int e = true_residual_run(b, s0, 1, s, b->FA, b->FA + b->h64, b->h64);
+        if (e != TM_OK) return e;
+    }
+    if (!j->raw_out) return TM_OK;
+    double *cpart = n > 1 ? (double *)(b->t + s0 * b->hsp) : b->cpart;
+    const void *links = b->G->links[P64];
+    RawOuts R{}, R2{};
+    for (int i = 0; i < n; i++) {
+        R.p[i] = b->slot_job[s0 + i]->raw_out;
+        R2.p[i] = b->slot_job[s0 + i]->raw_out2;
+    }
+    if (j->oet) {
+        // one-end trick (see harvest_lp_run)
+        char *re = b->FA, *ro = b->FB;
+        dsl_run(b, P64, false, EPI_PLAIN, CM_M, 0, s.so, w, s.se, w, re, w, j->kappa, 0.0, n);
+        dsl_run(b, P64, false, EPI_PLAIN, CM_M, 1, s.se, w, s.so, w, ro, w, j->kappa, 0.0, n);
+        launch_contract_lr(P64, g, links, s.se, s.so, w, s.se, s.so, w, cpart, R, n, 0.0, -2.0 * j->a, st, j->local_only);
+        launch_contract_lr(P64, g, links, re, ro, w, s.se, s.so, w, cpart, R2, n, 2.0, 0.0, st, j->local_only);
+        return TM_OK;
+    }
+    if (j->local_only) launch_contract_local(P64, g, s.se, s.so, w, codes, cpart, R, n, st);
+    else launch_contract(P64, g, links, s.se, s.so, w, codes, cpart, R, n, st);
+    if (j->hpe) {
+        // (BH)^4 s (see harvest_lp_run): even part through FA into FB, odd part
+        // through FA into the array of s_o
+        char *ta = b->FA, *we = b->FB, *wo = s.so;
+        auto bh = [&](int par, const char *in, char *out) {
+            dsl_run(b, P64, false, EPI_PLAIN, CM_BH, par, in, w, nullptr, 0, out, w, j->kappa, j->a, n);
+        };
+        bh(1, s.se, ta);
+        bh(0, ta, we);
+        bh(1, we, ta);
+        bh(0, ta, we);
+        bh(0, s.so, ta);
+        bh(1, ta, wo);
+        bh(0, wo, ta);
+        bh(1, ta, wo);
+        launch_contract_local(P64, g, we, wo, w, codes, cpart, R2, n, st);
+    }
     return TM_OK;
 }
 
@@ -797,7 +765,7 @@ int batch_process(Batch *b, std::vector<Job *> &finished)
         reliable_update_run(b, s, n);
         s += n;
     }
-    // finished slots; LP noise solves harvested together
+    // finished slots, harvested in runs
     auto done = [&](int s) {
         const int st = b->st_h[s].status;
         return b->slot_job[s] && st != ST_RUNNING && st != ST_NEED_UPDATE;
@@ -808,21 +776,27 @@ int batch_process(Batch *b, std::vector<Job *> &finished)
             continue;
         }
         Job *j = b->slot_job[s];
+        static const int cap_env = run_cap("TM_HARVEST_RUN");
+        const bool lp = lp_harvest(b, j);
+        int cap = std::min(b->wslots, cap_env);
+        if (!j->noise) cap = std::min(run_slots64(b), cap_env);
+        else if (!lp && (j->want_true || contract_part_doubles(b->G->g) * sizeof(double) > b->hsp)) cap = 1;
+        auto joins = [&](const Job *k, int i) {
+            if (!j->noise) return next_user(b, j, k, i);
+            return k->noise && lp_harvest(b, k) == lp && prep_prec(b, k) == prep_prec(b, j) && same_params(k, j) &&
+                   k->oet == j->oet && k->hpe == j->hpe && k->local_only == j->local_only &&
+                   k->want_true == j->want_true && !k->raw_out == !j->raw_out;
+        };
         int n = 1;
-        if (lp_harvest(b, j)) {
-            static const int cap = run_cap("TM_HARVEST_RUN");
-            while (s + n < S && n < std::min(b->wslots, cap) && done(s + n) && lp_harvest(b, b->slot_job[s + n]) &&
-                   same_params(b->slot_job[s + n], j) && b->slot_job[s + n]->oet == j->oet &&
-                   b->slot_job[s + n]->hpe == j->hpe && b->slot_job[s + n]->local_only == j->local_only)
-                n++;
-            harvest_lp_run(b, s, n);
-        } else if (prep_prec(b, j) != P32) {
-            harvest64(b, s, b->st_h[s], j);
-        }
+        while (s + n < S && n < cap && done(s + n) && joins(b->slot_job[s + n], n)) n++;
+        int e = TM_OK;
+        if (!j->noise) e = harvest_user_run(b, s, n);
+        else if (lp) harvest_lp_run(b, s, n);
+        else if (prep_prec(b, j) != P32) e = harvest64_run(b, s, n);
+        if (e != TM_OK) rc = e;
         for (int i = 0; i < n; i++) {
             Job *ji = b->slot_job[s + i];
-            int e = harvest_done(b, s + i, b->st_h[s + i]);
-            if (e != TM_OK) rc = e;
+            harvest_done(b, s + i, b->st_h[s + i]);
             finished.push_back(ji);
         }
         s += n;

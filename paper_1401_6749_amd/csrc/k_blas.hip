@@ -407,49 +407,29 @@ void launch_accum_x(const Geom &g, char *x64, size_t s64, const char *x32_in, ch
         hipLaunchKernelGGL(k_accum_x, dim3(nblk_of(g), n), dim3(BLOCK), 0, s, g, x64, x32_in, x32_zero, s64, s32);
 }
 
-// per-tile |f|^2 of one FP64 half field: partial[tile], 64-site tiles (the
-// partials beyond the last tile, of a walk with partly filled waves, are zero)
-__global__ __launch_bounds__(BLOCK) void k_norm_partial(Geom g, const char *f, double *partial, int ntile)
+// |f|^2 of FP64 half fields per 64-site tile (the partials beyond the last
+// tile, of a walk with partly filled waves, are zero); blockIdx.y = field
+__global__ __launch_bounds__(BLOCK) void k_norm_partial(Geom g, const char *f, size_t pitch, double *partial,
+                                                        int ntile)
 {
     const int cb = blockIdx.x * BLOCK + threadIdx.x;
     double part = 0.0;
     if (cb < g.vh) {
         cpx<double> v[12];
-        SpinorIO<P64>::load(f, g.vh, cb, v);
+        SpinorIO<P64>::load(f + (size_t)blockIdx.y * pitch, g.vh, cb, v);
 #pragma unroll
         for (int k = 0; k < 12; k++) part += norm2(v[k]);
     }
     part = wave_sum(part);
     const int tile = cb / TILE;
-    if ((threadIdx.x & 63) == 0 && tile < ntile) partial[tile] = part;
+    if ((threadIdx.x & 63) == 0 && tile < ntile) partial[(size_t)blockIdx.y * ntile + tile] = part;
 }
 
-void launch_norm_partial(const Geom &g, const char *f, double *partial, hipStream_t s)
+void launch_norm_partial(const Geom &g, const char *f, size_t pitch, int n, double *partial, hipStream_t s)
 {
     const int nt = ntile_of(g);
-    hipLaunchKernelGGL(k_norm_partial, dim3((nt * TILE + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, g, f, partial, nt);
-}
-
-__global__ __launch_bounds__(BLOCK) void k_site_diag(Geom g, int mode, double a, const char *in, char *out)
-{
-    const int cb = blockIdx.x * BLOCK + threadIdx.x;
-    if (cb >= g.vh) return;
-    cpx<double> v[12];
-    SpinorIO<P64>::load(in, g.vh, cb, v);
-    if (mode == 1) {
-        const double den = 1.0 / (1.0 + a * a);
-#pragma unroll
-        for (int k = 0; k < 12; k++) {
-            const double ch = k < 6 ? 1.0 : -1.0;
-            v[k] = cmul(cpx<double>{den, -ch * a * den}, v[k]);
-        }
-    }
-    SpinorIO<P64>::store(out, g.vh, cb, v);
-}
-
-void launch_site_diag(const Geom &g, int mode, double a, const char *in, char *out, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_site_diag, dim3(nblk_of(g)), dim3(BLOCK), 0, s, g, mode, a, in, out);
+    hipLaunchKernelGGL(k_norm_partial, dim3((nt * TILE + BLOCK - 1) / BLOCK, n), dim3(BLOCK), 0, s, g, f, pitch,
+                       partial, nt);
 }
 
 // ---------------------------------------------------------------------------

@@ -612,7 +612,8 @@ __device__ __forceinline__ double epilogue(const DslashArgs &A, int slot, int cb
             v[k] = b[k] - v[k];
             part += (double)norm2(v[k]);
         }
-        SpinorIO<SP>::template store<T, NT>(A.out + (size_t)slot * A.out_slot, vh, cb, v);
+        // a check of the residual wants its norm only
+        if (A.out) SpinorIO<SP>::template store<T, NT>(A.out + (size_t)slot * A.out_slot, vh, cb, v);
     }
     return part;
 }

@@ -56,10 +56,12 @@ void launch_gauge_pack(int p, const Geom &g, const double *canon, void *out, hip
     }
 }
 
-// canonical spinor [V][4][3][2] <-> layout; full field = even half, odd half
+// canonical spinor [V][4][3][2] <-> layout: field i's halves at fe + i * pitch
+// and fo + i * pitch.  IMPORT with ainv: the odd half is A^-1 times the
+// spinor (A = 1 + i a g5), the hop input of a solve's preparation.
 template <int P, bool IMPORT>
-__global__ __launch_bounds__(BLOCK) void k_field_conv(Geom g, const double *canon_in, double *canon_out,
-                                                      const char *fin, char *fout, size_t fbytes)
+__global__ __launch_bounds__(BLOCK) void k_field_conv(Geom g, double *canon, char *fe, char *fo, size_t pitch,
+                                                      int ainv, double a)
 {
     const int cb = blockIdx.x * BLOCK + threadIdx.x;
     const int par = blockIdx.y & 1, rhs = blockIdx.y >> 1;
@@ -67,41 +69,73 @@ __global__ __launch_bounds__(BLOCK) void k_field_conv(Geom g, const double *cano
     const Site s = site_of(g, cb, par);
     const size_t lex = (size_t)lex_of(g, s);
     const size_t V = (size_t)2 * g.vh;
-    const size_t hb = half_bytes(P, g);
+    char *f = (par ? fo : fe) + (size_t)rhs * pitch;
+    double2 *c = (double2 *)canon + ((size_t)rhs * V + lex) * 12;
+    cpx<double> v[12];
     if (IMPORT) {
-        const double2 *c = (const double2 *)canon_in + ((size_t)rhs * V + lex) * 12;
-        cpx<double> v[12];
         for (int k = 0; k < 12; k++) v[k] = cpx<double>{c[k].x, c[k].y};
-        SpinorIO<P>::store(fout + (size_t)rhs * fbytes + par * hb, g.vh, cb, v);
+        if (ainv && par) {
+            const double den = 1.0 / (1.0 + a * a);
+            for (int k = 0; k < 12; k++) v[k] = cmul(cpx<double>{den, (k < 6 ? -a : a) * den}, v[k]);
+        }
+        SpinorIO<P>::store(f, g.vh, cb, v);
     } else {
-        cpx<double> v[12];
-        SpinorIO<P>::load(fin + (size_t)rhs * fbytes + par * hb, g.vh, cb, v);
-        double2 *c = (double2 *)canon_out + ((size_t)rhs * V + lex) * 12;
+        SpinorIO<P>::load(f, g.vh, cb, v);
         for (int k = 0; k < 12; k++) c[k] = make_double2(v[k].re, v[k].im);
     }
 }
 
+// FP64 halves with pitches of their own -> canonical
+__global__ __launch_bounds__(BLOCK) void k_halves_export(Geom g, double *canon, const char *fe, size_t pe,
+                                                         const char *fo, size_t po)
+{
+    const int cb = blockIdx.x * BLOCK + threadIdx.x;
+    const int par = blockIdx.y & 1, rhs = blockIdx.y >> 1;
+    if (cb >= g.vh) return;
+    const Site s = site_of(g, cb, par);
+    double2 *c = (double2 *)canon + ((size_t)rhs * 2 * g.vh + (size_t)lex_of(g, s)) * 12;
+    cpx<double> v[12];
+    SpinorIO<P64>::load(par ? fo + rhs * po : fe + rhs * pe, g.vh, cb, v);
+    for (int k = 0; k < 12; k++) c[k] = make_double2(v[k].re, v[k].im);
+}
+
 template <bool IMPORT>
-static void field_conv(int p, const Geom &g, int nrhs, const double *ci, double *co, const char *fi, char *fo,
-                       hipStream_t s)
+static void field_conv(int p, const Geom &g, int nrhs, double *canon, char *fe, char *fo, size_t pitch, int ainv,
+                       double a, hipStream_t s)
 {
     dim3 grid(nblk_of(g), 2 * nrhs);
-    const size_t fb = 2 * half_bytes(p, g);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, s, g, canon, fe, fo, pitch, ainv, a);
+    };
     switch (p) {
-    case P64: hipLaunchKernelGGL((k_field_conv<P64, IMPORT>), grid, dim3(BLOCK), 0, s, g, ci, co, fi, fo, fb); break;
-    case P32: hipLaunchKernelGGL((k_field_conv<P32, IMPORT>), grid, dim3(BLOCK), 0, s, g, ci, co, fi, fo, fb); break;
-    case P16: hipLaunchKernelGGL((k_field_conv<P16, IMPORT>), grid, dim3(BLOCK), 0, s, g, ci, co, fi, fo, fb); break;
-    case PBF: hipLaunchKernelGGL((k_field_conv<PBF, IMPORT>), grid, dim3(BLOCK), 0, s, g, ci, co, fi, fo, fb); break;
+    case P64: go(k_field_conv<P64, IMPORT>); break;
+    case P32: go(k_field_conv<P32, IMPORT>); break;
+    case P16: go(k_field_conv<P16, IMPORT>); break;
+    case PBF: go(k_field_conv<PBF, IMPORT>); break;
     }
 }
 
 void launch_field_import(int p, const Geom &g, int nrhs, const double *canon, char *field, hipStream_t s)
 {
-    field_conv<true>(p, g, nrhs, canon, nullptr, nullptr, field, s);
+    const size_t hb = half_bytes(p, g);
+    field_conv<true>(p, g, nrhs, const_cast<double *>(canon), field, field + hb, 2 * hb, 0, 0.0, s);
 }
 void launch_field_export(int p, const Geom &g, int nrhs, const char *field, double *canon, hipStream_t s)
 {
-    field_conv<false>(p, g, nrhs, nullptr, canon, field, nullptr, s);
+    const size_t hb = half_bytes(p, g);
+    char *f = const_cast<char *>(field);
+    field_conv<false>(p, g, nrhs, canon, f, f + hb, 2 * hb, 0, 0.0, s);
+}
+void launch_eta_import(const Geom &g, int n, const double *canon, char *even, char *odd, size_t pitch, bool ainv,
+                       double a, hipStream_t s)
+{
+    field_conv<true>(P64, g, n, const_cast<double *>(canon), even, odd, pitch, ainv ? 1 : 0, a, s);
+}
+void launch_halves_export(const Geom &g, int n, const char *even, size_t even_pitch, const char *odd, size_t odd_pitch,
+                          double *canon, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_halves_export, dim3(nblk_of(g), 2 * n), dim3(BLOCK), 0, s, g, canon, even, even_pitch, odd,
+                       odd_pitch);
 }
 
 }  // namespace tmk

@@ -79,7 +79,7 @@ struct Batch {
     char *x64 = nullptr, *b64 = nullptr;
     uint32_t *codes = nullptr;
     char *FA = nullptr, *FB = nullptr, *FC = nullptr;  // scratch: FP64 full field [even | odd], or per-slot halves
-    char *FD = nullptr;       // fourth per-slot scratch half (low-precision kinds: one-end trick)
+    char *FD = nullptr;       // fourth scratch array (low-precision kinds)
     int wpp = tmk::P64;       // precision of the per-slot scratch halves
     size_t wpitch = 0;        // their slot pitch
     int wslots = 1;           // slots a run may span
@@ -107,9 +107,8 @@ size_t batch_footprint(const tm_gauge *G, Kind kind, int S);
 int batch_create(tm_context *ctx, const tm_gauge *G, Kind kind, int S, int chunk, hipStream_t stream, Batch **out,
                  const Mem *mem = nullptr);
 void batch_destroy(Batch *b);
-int batch_fill(Batch *b, int slot, Job *j);
-// place up to n jobs into free slots (noise solves with equal kappa, a in
-// consecutive slots are prepared together); returns the number placed
+// place up to n jobs into free slots (jobs with equal kappa, a in consecutive
+// slots are prepared together); returns the number placed
 int batch_fill_many(Batch *b, Job *const *jobs, int n);
 int batch_launch_chunk(Batch *b);
 // after the chunk's event completed: reliable updates and harvests; fills

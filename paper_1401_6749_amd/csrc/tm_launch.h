@@ -122,10 +122,8 @@ void launch_cg_start(int pin, int pout, const Geom &g, const char *in, size_t in
 // x64 += x32; x32 = 0 (if x32_zero), n consecutive slots with strides s64, s32
 void launch_accum_x(const Geom &g, char *x64, size_t s64, const char *x32_in, char *x32_zero, size_t s32, int n,
                     hipStream_t s);
-// per-tile (64 sites) |f|^2 partials of one FP64 half field
-void launch_norm_partial(const Geom &g, const char *f, double *partial, hipStream_t s);
-// out = c * in with c per chirality: A^-1 (mode 1) or identity (mode 0), FP64
-void launch_site_diag(const Geom &g, int mode, double a, const char *in, char *out, hipStream_t s);
+// |f|^2 partials (ntile_of per field) of n FP64 half fields, pitch bytes apart
+void launch_norm_partial(const Geom &g, const char *f, size_t pitch, int n, double *partial, hipStream_t s);
 
 // ---- noise ----
 // Z4 codes of both parities: codes[par*vh + cb]
@@ -186,6 +184,14 @@ void launch_gauge_pack(int p, const Geom &g, const double *canon, void *out, hip
 // canonical full-lattice spinors <-> layout (full field = even half, then odd half)
 void launch_field_import(int p, const Geom &g, int nrhs, const double *canon, char *field, hipStream_t s);
 void launch_field_export(int p, const Geom &g, int nrhs, const char *field, double *canon, hipStream_t s);
+
+// n consecutive canonical FP64 sources into FP64 halves even + i * pitch and
+// odd + i * pitch (the odd half times A^-1 with ainv)
+void launch_eta_import(const Geom &g, int n, const double *canon, char *even, char *odd, size_t pitch, bool ainv,
+                       double a, hipStream_t s);
+// n FP64 fields from halves with pitches of their own to consecutive canonical ones
+void launch_halves_export(const Geom &g, int n, const char *even, size_t even_pitch, const char *odd, size_t odd_pitch,
+                          double *canon, hipStream_t s);
 
 // streaming copy probe
 void launch_stream_copy(const void *src, void *dst, size_t bytes, hipStream_t s);

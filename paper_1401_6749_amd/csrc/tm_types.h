@@ -115,7 +115,7 @@ enum : int {
     EPI_PLAIN = 0,  // out = P in2 + Q hop
     EPI_NORM = 1,   // as PLAIN, plus per-block |out|^2
     EPI_CGUPD = 2,  // Ap = P in2 + Q hop; r -= alpha Ap; per-block |r|^2 (x += alpha p in the direction update)
-    EPI_RESID = 3,  // out = b - (P in2 + Q hop); per-block |out|^2
+    EPI_RESID = 3,  // out = b - (P in2 + Q hop), not stored if out is null; per-block |out|^2
     EPI_START = 4   // v = P in2 + Q hop; r = out = v and x = 0 in the CG storage precision; per-block |v|^2
 };
 
