@@ -1195,12 +1195,12 @@ inline int walk_length(const Geom &g, const WalkPlan &p, int nslot, int waves)
     return len;
 }
 
-// Most reduction tiles x right-hand sides of a launch on k_dslash_split: one
-// block per CU.  Both parities of a hop: 64 tiles (8^3x16, one FP64 right-hand
-// side) 10.7 us against the walk's 17.4 us; 768 tiles (12 of them) 26.4
-// against 21.5 us, as each block then reads its neighbours from L2 where the
-// walk has them in LDS.
-constexpr int SPLIT_MOST = 256;
+// Most reduction tiles x right-hand sides of a launch on k_dslash_split: two
+// blocks per CU.  Both parities of a hop with one FP64 right-hand side: 64 tiles
+// (8^3x16) 10.7 us against the walk's 17.4 us, 384 tiles (12^3x24) 18.5 against
+// 21.2 us; 768 tiles (12 of them at 8^3x16) 26.4 against 21.5 us, as each block
+// then reads its neighbours from L2 where the walk has them in LDS.
+constexpr int SPLIT_MOST = 512;
 
 template <int SP, bool DAG, int EPI, bool IN2, int SRC = 0, int PO = SP>
 static bool launch_walk(DslashArgs A, hipStream_t s)
