@@ -77,15 +77,20 @@ size_t batch_footprint(const tm_gauge *G, Kind kind, int S)
     return b;
 }
 
+// Iterations per launch chunk: a few milliseconds of device work between host
+// checks, 4 to 8 iterations.  On small lattices, where an iteration takes tens
+// of microseconds, longer chunks cost more in iterations launched after the
+// last solve has stopped, and in a larger graph to build, than the checks they
+// save (up to 64 -> up to 8: FP64 solve of 39 iterations at 8^3x16 2.58 -> 1.72
+// ms; 12 FP16 solves of 7 iterations there 3.11 -> 1.86 ms).
 int auto_chunk(const tm_gauge *G, Kind k, int S)
 {
-    // aim at a few milliseconds of device work between host checks
     const int sp = kind_prec(k);
     const double lb = sp == P64 ? 96 : sp == P32 ? 48 : 36, sb = sp == P64 ? 192 : sp == P32 ? 96 : 52;
     const double bytes_it = (double)G->g.vh * S * (32.0 * lb / 4.0 + 20.0 * sb);
     const double secs = bytes_it / 4.0e12 + 8 * 3e-6;
     int c = (int)(3e-3 / secs);
-    return std::max(4, std::min(64, c));
+    return std::max(4, std::min(8, c));
 }
 
 static char *carve(char *&cur, size_t bytes)
