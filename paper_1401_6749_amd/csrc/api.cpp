@@ -515,15 +515,11 @@ static int dslash_impl(tm_context *ctx, const tm_gauge *G, tm_op op, double kapp
         const int coef = op == TM_OP_HOP ? CM_HOP : op == TM_OP_M ? CM_M : op == TM_OP_BH ? CM_BH : CM_MDAG;
         const bool dag = op == TM_OP_MDAG;
         const bool in2 = op == TM_OP_M || op == TM_OP_MDAG;
-        for (int par = 0; par < 2; par++) {
-            A.in = ic + (1 - par) * hb;
-            A.in2_slot = in_stride;
-            A.in2 = in2 ? ic + par * hb : nullptr;
-            A.out = oc + par * hb;
-            A.out_par = par;
-            A.coef = coef;
-            launch_dslash(p, dag, EPI_PLAIN, in2, A, s);
-        }
+        A.in = ic;
+        A.in2 = in2 ? ic : nullptr;
+        A.out = oc;
+        A.coef = coef;
+        launch_dslash_full(p, dag, in2, A, s);
     } else {
         // temporaries: odd half per rhs, plus an even half per rhs for MHAT_DAG_MHAT
         const size_t need = dslash_tmp_bytes(G, p, op, nrhs);

@@ -881,19 +881,36 @@ constexpr int walk_waves()
                        : EPI == EPI_CGUPD ? TM_WALK_WAVES_F16_CG : TM_WALK_WAVES_F16;
 }
 
+// Both output parities of a full field in one launch (par_bytes): selects the
+// halves of the block and returns its site block within the parity.
+__device__ __forceinline__ int pick_parity(DslashArgs &A, int sb)
+{
+    if (!A.par_bytes) return sb;
+    const int par = A.par_pairs ? sb & 1 : sb >= A.nblk_site;
+    A.in += (1 - par) * A.par_bytes;
+    A.in2 += par * A.par_bytes;
+    A.out += par * A.par_bytes;
+    A.out_par = par;
+    return A.par_pairs ? sb >> 1 : sb - par * A.nblk_site;
+}
+
 // SRC bit 1: the site-local input is eta decoded from Z4 codes (the
 // reconstruction of noise solves), as in k_dslash.
 // PART: the chunk's last wave is partly filled; its lanes beyond the last site
 // follow that site and write nothing (a variant of its own, because the masks
 // cost the full chunks 1.5% of the 12-RHS FP16 hop).
 template <int SP, bool DAG, int EPI, bool IN2, bool SLOT, bool NT, int SRC = 0, int PO = SP, bool PART = false>
-__global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_walk(const DslashArgs A)
+__global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_walk(const DslashArgs A0)
 {
     using T = typename Real<SP>::T;
     using RawT = typename RawSel<SP, T>::type;
     __shared__ WalkBuf<SP> W;
     int sb, slot;
-    if (!map_block(A.nblk_site, A.nslot, A.swz, sb, slot, A.gouter != 0)) return;
+    constexpr bool BOTH = EPI == EPI_PLAIN && !SLOT && SRC == 0;
+    if (!map_block(BOTH && A0.par_bytes ? 2 * A0.nblk_site : A0.nblk_site, A0.nslot, A0.swz, sb, slot, A0.gouter != 0))
+        return;
+    DslashArgs A = A0;
+    if constexpr (BOTH) sb = pick_parity(A, sb);
     double kappa = A.kappa_u, a = A.a_u, alpha = 0;
     if constexpr (SLOT) {
         const SlotState &st = A.st[slot];
@@ -1056,12 +1073,15 @@ __device__ __forceinline__ void split_dir(const DslashArgs &A, const HopRes &R, 
 }
 
 template <int SP, bool DAG, int EPI, bool IN2, bool SLOT, int SRC = 0, int PO = SP>
-__global__ __launch_bounds__(512, (SP == P64 ? 2 : 4)) void k_dslash_split(const DslashArgs A)
+__global__ __launch_bounds__(512, (SP == P64 ? 2 : 4)) void k_dslash_split(const DslashArgs A0)
 {
     using T = typename Real<SP>::T;
     __shared__ cpx<T> half[8][6][64];
     int tile, slot;
-    if (!map_block(A.nblk_site, A.nslot, A.swz, tile, slot)) return;
+    constexpr bool BOTH = EPI == EPI_PLAIN && !SLOT && SRC == 0;
+    if (!map_block(BOTH && A0.par_bytes ? 2 * A0.nblk_site : A0.nblk_site, A0.nslot, A0.swz, tile, slot)) return;
+    DslashArgs A = A0;
+    if constexpr (BOTH) tile = pick_parity(A, tile);
     double kappa = A.kappa_u, a = A.a_u, alpha = 0;
     if constexpr (SLOT) {
         const SlotState &st = A.st[slot];
@@ -1170,7 +1190,7 @@ inline int lanes_per_site(int nslot)
 
 // Timeslices walked per block, a divisor of Lt up to 8 (TM_LDS_TWALK).  A block
 // that walks tw timeslices takes tw + 1 steps (its first loads stage two
-// timeslices), and the chip runs 256 CUs x 4 SIMDs x waves at a time, so the
+// timeslices), and each of the 256 CUs runs 4 SIMDs x waves at a time, so the
 // walk is the longest that does not lengthen rounds x (tw + 1).  Long walks
 // pay on large launches (12 FP32 right-hand sides at 32^3x64, both parities:
 // 8 / 4 / 2 / 1 timeslices 1688 / 1728 / 1878 / 2225 us); on small ones they
@@ -1179,7 +1199,7 @@ inline int lanes_per_site(int nslot)
 inline int walk_length(const Geom &g, const WalkPlan &p, int nslot, int waves)
 {
     static const int most = std::max(1, env_knob("TM_LDS_TWALK", 8));
-    const double cap = 1024.0 * waves / (p.threads / 64);
+    const double cap = 256 * std::max(1, 4 * waves / (p.threads / 64));  // blocks at a time
     double best = 1e30;
     int len = 1;
     for (int tw = std::min(most, g.L[3]); tw >= 1; tw--) {
@@ -1202,6 +1222,15 @@ inline int walk_length(const Geom &g, const WalkPlan &p, int nslot, int waves)
 // then reads its neighbours from L2 where the walk has them in LDS.
 constexpr int SPLIT_MOST = 512;
 
+// Right-hand sides up to which the two parities of a site block run next to
+// each other (on one XCD, in turn): they read the same links, which few
+// right-hand sides do not amortise otherwise.  Both parities of a hop at
+// 32^3x64, side by side against one after the other: FP64, one right-hand side
+// 349 against 387 us; 12 of them 3402 against 3312 us, as the blocks in flight
+// then cover half the neighbourhood.  At 16^3x32, four of them: 59.3 against
+// 62.7 us.
+constexpr int PAIR_MOST = 6;
+
 template <int SP, bool DAG, int EPI, bool IN2, int SRC = 0, int PO = SP>
 static bool launch_walk(DslashArgs A, hipStream_t s)
 {
@@ -1211,16 +1240,18 @@ static bool launch_walk(DslashArgs A, hipStream_t s)
         if (!plan.tiles || field >= (1ull << 32)) return false;
         A.wcy = plan.cy;
         A.wcz = plan.cz;
-        if (plan.tiles * A.nslot <= SPLIT_MOST) {
+        const int npar = A.par_bytes ? 2 : 1;
+        A.par_pairs = A.nslot <= PAIR_MOST;
+        if (plan.tiles * A.nslot * npar <= SPLIT_MOST) {
             A.in_span = (uint32_t)field;
             A.gauge_span = (uint32_t)std::min<uint64_t>((uint64_t)2 * 4 * A.g.vh * link_bytes(SP), 0xFFFFFFFFull);
             A.nblk_site = A.ntile = plan.tiles;
-            const int total = plan.tiles * A.nslot, grid = A.swz ? 8 * ((total + 7) / 8) : total;
+            const int total = plan.tiles * A.nslot * npar, grid = A.swz ? 8 * ((total + 7) / 8) : total;
             if (A.st) hipLaunchKernelGGL((k_dslash_split<SP, DAG, EPI, IN2, PO == SP && SRC == 0, SRC, PO>), dim3(grid), dim3(512), 0, s, A);
             else hipLaunchKernelGGL((k_dslash_split<SP, DAG, EPI, IN2, false, SRC, PO>), dim3(grid), dim3(512), 0, s, A);
             return true;
         }
-        const int tw = walk_length(A.g, plan, A.nslot, walk_waves<SP, EPI>());
+        const int tw = walk_length(A.g, plan, A.nslot * npar, walk_waves<SP, EPI>());
         A.twalk = tw;
         A.in_span = (uint32_t)field;
         A.gauge_span = (uint32_t)std::min<uint64_t>(
@@ -1229,7 +1260,7 @@ static bool launch_walk(DslashArgs A, hipStream_t s)
         A.gouter = gouter;
         A.nblk_site = plan.chunks * (A.g.L[3] / tw);
         A.ntile = plan.tiles;
-        const int total = A.nblk_site * A.nslot;
+        const int total = A.nblk_site * A.nslot * npar;
         const int grid = A.swz ? 8 * ((total + 7) / 8) : total;
         const bool part = plan.cy * plan.cz * A.g.lxh != plan.threads;
         // outputs are streamed past L2 (non-temporal), keeping it for the halo lines
@@ -1252,6 +1283,19 @@ template <int SP, bool DAG, int EPI, bool IN2>
 static void launch_t(DslashArgs A, hipStream_t s)
 {
     if (launch_walk<SP, DAG, EPI, IN2>(A, s)) return;
+    if (A.par_bytes) {  // the register kernel takes one parity at a time
+        const size_t hb = A.par_bytes;
+        A.par_bytes = 0;
+        for (int par = 0; par < 2; par++) {
+            DslashArgs B = A;
+            B.in += (1 - par) * hb;
+            B.in2 += par * hb;
+            B.out += par * hb;
+            B.out_par = par;
+            launch_t<SP, DAG, EPI, IN2>(B, s);
+        }
+        return;
+    }
     int R = lanes_per_site(A.nslot);
     // 32-bit buffer offsets: the R input fields of a group must span < 4 GiB
     const uint64_t field = (uint64_t)A.g.vh * (SP == P64 ? 192 : SP == P32 ? 96 : 52);
@@ -1342,6 +1386,12 @@ int launch_dslash_start(int sp, int po, const DslashArgs &A, hipStream_t s)
     else if (sp == P16 && po == P16) ok = launch_walk<P16, true, EPI_START, true, 0, P16>(B, s);
     else if (sp == PBF && po == PBF) ok = launch_walk<PBF, true, EPI_START, true, 0, PBF>(B, s);
     return ok ? 0 : -1;
+}
+
+int launch_dslash_full(int sp, bool dag, bool in2, DslashArgs A, hipStream_t s)
+{
+    A.par_bytes = half_bytes(sp, A.g);
+    return launch_dslash(sp, dag, EPI_PLAIN, in2, A, s);
 }
 
 int launch_dslash(int sp, bool dag, int epi, bool in2, const DslashArgs &A, hipStream_t s)

@@ -66,6 +66,9 @@ inline WalkPlan walk_plan(const Geom &g)
 // in the CG update (links of the same precision).  Returns -1 on an
 // unsupported combination.
 int launch_dslash(int sp, bool dag, int epi, bool in2, const DslashArgs &A, hipStream_t s);
+// plain Dslash on full fields (A.in, A.in2, A.out), both output parities in
+// one launch where the timeslice walk serves the lattice, else in two
+int launch_dslash_full(int sp, bool dag, bool in2, DslashArgs A, hipStream_t s);
 // the last preparation Dslash of a noise run with EPI_START: v = Mhat^dag bhat
 // (A.in = A^-dag D'_oe bhat, A.in2 = bhat, both in precision sp: P32, or the
 // half precision po itself) written as r (A.r), p (A.out) and x = 0 (A.x) in

@@ -131,10 +131,13 @@ struct DslashArgs {
     char *out;
     size_t in_slot, in2_slot, out_slot;  // bytes between consecutive slots
     int out_par;
+    size_t par_bytes;  // not 0: both output parities in one launch; in, in2 and out are full fields, their
+                       // odd halves par_bytes after the even ones (launch_dslash_full)
+    int par_pairs;     // the two parities of a site block run next to each other (set by the launcher)
     int coef;
     double kappa_u, a_u;  // used when st == nullptr
     SlotState *st;
-    int nslot, nblk_site, swz;  // nblk_site: blocks over the sites (set by the launcher)
+    int nslot, nblk_site, swz;  // nblk_site: blocks over the sites of one parity (set by the launcher)
     int ntile;                  // reduction tiles per slot (one per wave of the walk, or per 64 sites)
     uint32_t in_span, gauge_span;  // bytes reachable through the buffer resources (set by the launcher)
     int twalk;                     // timeslices walked per block (set by the launcher)

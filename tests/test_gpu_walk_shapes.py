@@ -58,3 +58,20 @@ def test_split_equals_walk(prec, dims):
         many = GU.apply_op(g, op, 0.14, 0.02, prec, psi, dims)
         for r in (0, 9):
             assert np.array_equal(many[r], GU.apply_op(g, op, 0.14, 0.02, prec, psi[r:r + 1], dims)[0]), (op, r)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f16", "bf16"])
+def test_full_operators_on_both_kernels(oracle, prec):
+    """B H over both parities in one launch: split kernel (1), walk with the
+    parities side by side (5) and one after the other (8 right-hand sides)."""
+    dims = (8, 8, 6, 12)
+    U = inputs.gauge_field(dims, seed=6)
+    g = GU.load(dims, U)
+    psi = np.stack([inputs.random_spinor(dims, 60 + r) for r in range(8)])
+    want = oracle.apply_bh(dims, -1, U, 0.14, 0.02, psi[0])
+    one = GU.apply_op(g, "bh", 0.14, 0.02, prec, psi[:1], dims)[0]
+    assert GU.relerr(one, want) < TOL[prec]
+    for n in (5, 8):
+        got = GU.apply_op(g, "bh", 0.14, 0.02, prec, psi[:n], dims)
+        assert np.array_equal(got[0], one)
+        assert np.array_equal(got[n - 1], GU.apply_op(g, "bh", 0.14, 0.02, prec, psi[n - 1:n], dims)[0])
