@@ -212,7 +212,10 @@ struct ArgCoef {
         return {has_x, true, c.alpha[slot], c.beta[slot]};
     }
 };
-template <int SP, int XR, class Coef>
+// Loads past the caches (STREAM 1: x and r, 2: p too) where the fields do not
+// fit the 256 MB last-level cache (update_stream): the reads then neither
+// allocate there nor push out the lines that others will hit.
+template <int SP, int XR, class Coef, int STREAM>
 __global__ __launch_bounds__(BLOCK) void k_p_update(Geom g, char *p, size_t p_slot, const char *r, size_t r_slot,
                                                     char *x, size_t x_slot, Coef coef, int nslot, int nblk,
                                                     int swz)
@@ -228,12 +231,12 @@ __global__ __launch_bounds__(BLOCK) void k_p_update(Geom g, char *p, size_t p_sl
     cpx<T> pv[12];
     char *ps = p + (size_t)slot * p_slot;
     char *xs = step ? x + (size_t)slot * x_slot : nullptr;
-    SpinorIO<SP>::load(ps, g.vh, cb, pv);
+    SpinorIO<SP>::template load<T, (STREAM > 1)>(ps, g.vh, cb, pv);
     // x and p are written with non-temporal stores: each is next read by a
     // later kernel, after far more data than the caches hold has passed
     if (step) {
         cpx<T> xv[12];
-        SpinorIO<XR>::load(xs, g.vh, cb, xv);
+        SpinorIO<XR>::template load<T, (STREAM > 0)>(xs, g.vh, cb, xv);
         const T al = (T)S.alpha;
 #pragma unroll
         for (int k = 0; k < 12; k++) xv[k] = xv[k] + cscale(al, pv[k]);
@@ -241,12 +244,22 @@ __global__ __launch_bounds__(BLOCK) void k_p_update(Geom g, char *p, size_t p_sl
     }
     if (run) {
         cpx<T> rv[12];
-        SpinorIO<XR>::load(r + (size_t)slot * r_slot, g.vh, cb, rv);
+        SpinorIO<XR>::template load<T, (STREAM > 0)>(r + (size_t)slot * r_slot, g.vh, cb, rv);
         const T beta = (T)S.beta;
 #pragma unroll
         for (int k = 0; k < 12; k++) pv[k] = rv[k] + cscale(beta, pv[k]);
         SpinorIO<SP>::template store<T, true>(ps, g.vh, cb, pv);
     }
+}
+
+// STREAM of an update of nslot fields of hb bytes.  Measured with ordinary
+// loads, x and r streamed, all streamed: 12 FP16 fields at 32^3x64 (1.96 GB of
+// p, r and x) 640, 613, 602 us; one FP64 field there (604 MB, p alone 201 MB)
+// 187, 145, 176 us; 12 FP32 fields at 16^3x32 (226 MB) 56, 57, 71 us.
+static int update_stream(size_t hb, int nslot)
+{
+    constexpr size_t LLC = (size_t)256 << 20;
+    return hb * nslot > LLC ? 2 : 3 * hb * nslot > LLC ? 1 : 0;
 }
 
 template <class Coef>
@@ -256,11 +269,17 @@ static void launch_p_update_t(int sp, int xr, const Geom &g, char *p, size_t p_s
     const int nblk = nblk_of(g);
     const int total = nblk * nslot;
     const int grid = swz ? 8 * ((total + 7) / 8) : total;
-#define TMK_P(SP, XR)                                                                                         \
-    if (sp == SP && xr == XR) {                                                                              \
-        hipLaunchKernelGGL((k_p_update<SP, XR, Coef>), dim3(grid), dim3(BLOCK), 0, s, g, p, p_slot, r, r_slot, \
-                           x, x_slot, coef, nslot, nblk, swz);                                                \
-        return;                                                                                               \
+    const int stream = update_stream(half_bytes(sp, g), nslot);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(BLOCK), 0, s, g, p, p_slot, r, r_slot, x, x_slot, coef, nslot, nblk,
+                           swz);
+    };
+#define TMK_P(SP, XR)                                        \
+    if (sp == SP && xr == XR) {                              \
+        if (stream == 2) go(k_p_update<SP, XR, Coef, 2>);    \
+        else if (stream) go(k_p_update<SP, XR, Coef, 1>);    \
+        else go(k_p_update<SP, XR, Coef, 0>);                \
+        return;                                              \
     }
     TMK_P(P64, P64)
     TMK_P(P32, P32)

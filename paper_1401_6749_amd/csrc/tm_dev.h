@@ -152,6 +152,22 @@ __device__ __forceinline__ void st4(void *p, uint32_t v)
     if constexpr (NT) __builtin_nontemporal_store(v, (uint32_t *)p);
     else *(uint32_t *)p = v;
 }
+// 16- and 4-byte global loads; NT for fields read once
+template <bool NT, class V>
+__device__ __forceinline__ V ld16(const V *p)
+{
+    if constexpr (!NT) return *p;
+    const tm_u32x4 u = __builtin_nontemporal_load((const tm_u32x4 *)p);
+    V v;
+    __builtin_memcpy(&v, &u, 16);
+    return v;
+}
+template <bool NT>
+__device__ __forceinline__ float ld4(const float *p)
+{
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    else return *p;
+}
 template <bool NT, class V>
 __device__ __forceinline__ void st16v(void *p, const V &v)
 {
@@ -163,13 +179,13 @@ __device__ __forceinline__ void st16v(void *p, const V &v)
 template <>
 struct SpinorIO<P64> {
     static constexpr size_t bytes_per_site = 192;
-    template <class T>
+    template <class T, bool NT = false>
     __device__ static __forceinline__ void load(const void *f, int vh, int i, cpx<T> v[12])
     {
         const double2 *p = (const double2 *)f;
 #pragma unroll
         for (int k = 0; k < 12; k++) {
-            double2 q = p[(size_t)k * vh + i];
+            const double2 q = ld16<NT>(&p[(size_t)k * vh + i]);
             v[k] = cpx<T>{(T)q.x, (T)q.y};
         }
     }
@@ -185,13 +201,13 @@ struct SpinorIO<P64> {
 template <>
 struct SpinorIO<P32> {
     static constexpr size_t bytes_per_site = 96;
-    template <class T>
+    template <class T, bool NT = false>
     __device__ static __forceinline__ void load(const void *f, int vh, int i, cpx<T> v[12])
     {
         const float4 *p = (const float4 *)f;
 #pragma unroll
         for (int g = 0; g < 6; g++) {
-            float4 q = p[(size_t)g * vh + i];
+            const float4 q = ld16<NT>(&p[(size_t)g * vh + i]);
             v[2 * g] = cpx<T>{(T)q.x, (T)q.y};
             v[2 * g + 1] = cpx<T>{(T)q.z, (T)q.w};
         }
@@ -223,14 +239,14 @@ struct HalfCodec<PBF> {
 template <int P>
 struct SpinorHalfIO {
     static constexpr size_t bytes_per_site = 52;
-    template <class T>
+    template <class T, bool NT = false>
     __device__ static __forceinline__ void load(const void *f, int vh, int i, cpx<T> v[12])
     {
         const uint4 *p = (const uint4 *)f;
-        const float sc = ((const float *)(p + 3 * (size_t)vh))[i];
+        const float sc = ld4<NT>((const float *)(p + 3 * (size_t)vh) + i);
 #pragma unroll
         for (int g = 0; g < 3; g++) {
-            uint4 q = p[(size_t)g * vh + i];
+            const uint4 q = ld16<NT>(&p[(size_t)g * vh + i]);
             uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
             for (int c = 0; c < 4; c++) {
