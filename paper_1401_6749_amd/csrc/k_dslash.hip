@@ -571,7 +571,18 @@ __device__ __forceinline__ double epilogue(const DslashArgs &A, int slot, int cb
         for (int k = 0; k < 12; k++) v[k] = cmul(Q[k / 6], acc[k]);
     }
     if (EPI == EPI_PLAIN || EPI == EPI_NORM) {
-        SpinorIO<SP>::template store<T, NT>(A.out + (size_t)slot * A.out_slot, vh, cb, v);
+        char *out = A.out + (size_t)slot * A.out_slot;
+        if constexpr (!NT || SP != P32) {
+            SpinorIO<SP>::template store<T, NT>(out, vh, cb, v);
+        } else if (!A.keep) {
+            // the empty statements keep the two branches' stores apart: merged,
+            // they would lose the hint
+            asm volatile("");
+            SpinorIO<SP>::template store<T, true>(out, vh, cb, v);
+            asm volatile("");
+        } else {
+            SpinorIO<SP>::template store<T, false>(out, vh, cb, v);
+        }
         if (EPI == EPI_NORM) {
 #pragma unroll
             for (int k = 0; k < 12; k++) part += (double)norm2(v[k]);
@@ -1263,7 +1274,14 @@ static bool launch_walk(DslashArgs A, hipStream_t s)
         const int total = A.nblk_site * A.nslot * npar;
         const int grid = A.swz ? 8 * ((total + 7) / 8) : total;
         const bool part = plan.cy * plan.cz * A.g.lxh != plan.threads;
-        // outputs are streamed past L2 (non-temporal), keeping it for the halo lines
+        // outputs are streamed past the caches (non-temporal), which keeps L2 for
+        // the halo lines, except FP32 ones that the next kernel can find in the
+        // last-level cache (256 MB) and the eight L2s (32 MB) do not hold either.
+        // Streamed / kept: FP32 Mhat, 12 right-hand sides, at 16^3x32 (75 MB) 98.8 /
+        // 96.0 us, at 24^3x48 (382 MB) 324 / 337 us.  In half precision and FP64 the
+        // choice at run time costs the large launches 1% for nothing gained.
+        const uint64_t written = field * A.nslot * npar;  // bytes
+        A.keep = written > (32u << 20) && written <= (128u << 20);
         auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(plan.threads), 0, s, A); };
         if constexpr (SRC != 0 || PO != SP) {
             if (part) go(k_dslash_walk<SP, DAG, EPI, IN2, false, true, SRC, PO, true>);

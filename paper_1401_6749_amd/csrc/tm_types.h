@@ -143,6 +143,7 @@ struct DslashArgs {
     int twalk;                     // timeslices walked per block (set by the launcher)
     int gouter;                    // slot groups slowest in the block order (set by the launcher)
     int wcy, wcz;                  // timeslice-walk chunk: y rows x z planes of full x rows (set by the launcher)
+    int keep;                      // FP32 plain and norm epilogues store through the caches (set by the launcher)
     double *partial;            // [nslot][ntile]
     // EPI_CGUPD (r), EPI_START (x, r)
     char *x, *r;
