@@ -469,14 +469,18 @@ static void enqueue_iteration(Batch *b)
     A.out_par = 0;
     A.coef = CM_MHAT;
     launch_dslash(sp, false, EPI_NORM, true, A, b->stream);
-    launch_cg_alpha(b->st, b->partial, b->S, b->nblk, b->stream);
+    // alpha, beside D3 where the walk serves the lattice
+    const bool beside = walk_plan(b->G->g).tiles > 0;
+    if (!beside) launch_cg_alpha(b->st, b->partial, b->S, b->nblk, b->stream);
     // D3
+    A.alpha_blocks = beside ? (b->S + 7) & ~7 : 0;
     A.in = b->u;
     A.in2 = nullptr;
     A.out = b->t;
     A.out_par = 1;
     A.coef = CM_AINV_DAG;
     launch_dslash(sp, true, EPI_PLAIN, false, A, b->stream);
+    A.alpha_blocks = 0;
     // D4 with the CG update
     A.in = b->t;
     A.in2 = b->u;

@@ -30,29 +30,9 @@ __device__ __forceinline__ double sum_fixed(const double *v, int n, double *lds)
     return block_sum<BLOCK>((a0 + a1) + (a2 + a3), lds);
 }
 
-__device__ __forceinline__ bool finite_pos(double v) { return v > 0.0 && v < 1.0e300; }
-
-__global__ __launch_bounds__(BLOCK) void k_cg_alpha(SlotState *st, const double *partial, int nblk)
+__global__ __launch_bounds__(64) void k_cg_alpha(SlotState *st, const double *partial, int nblk)
 {
-    __shared__ double lds[BLOCK / 64];
-    const int slot = blockIdx.x;
-    SlotState &S = st[slot];
-    if (S.status != ST_RUNNING) {
-        if (threadIdx.x == 0) S.xpend = 0;  // no step this iteration
-        return;
-    }
-    const double pap = sum_fixed(partial + (size_t)slot * nblk, nblk, lds);
-    if (threadIdx.x == 0) {
-        S.pap = pap;
-        if (!finite_pos(pap)) {
-            S.status = ST_NUMERIC;
-            S.alpha = 0.0;
-            S.xpend = 0;
-        } else {
-            S.alpha = S.rr / pap;
-            S.xpend = 1;
-        }
-    }
+    cg_alpha_wave(st[blockIdx.x], partial + (size_t)blockIdx.x * nblk, nblk);
 }
 
 __global__ __launch_bounds__(BLOCK) void k_cg_beta(SlotState *st, const double *partial, int nblk)
@@ -151,7 +131,7 @@ __global__ void k_reduce(const double *partial, int nblk, double *out)
 
 void launch_cg_alpha(SlotState *st, const double *partial, int nslot, int nblk, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_cg_alpha, dim3(nslot), dim3(BLOCK), 0, s, st, partial, nblk);
+    hipLaunchKernelGGL(k_cg_alpha, dim3(nslot), dim3(64), 0, s, st, partial, nblk);
 }
 void launch_cg_beta(SlotState *st, const double *partial, int nslot, int nblk, hipStream_t s)
 {

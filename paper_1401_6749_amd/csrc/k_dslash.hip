@@ -819,6 +819,23 @@ struct WalkBuf<P16> : WalkBufHalf<P16> {};
 template <>
 struct WalkBuf<PBF> : WalkBufHalf<PBF> {};
 
+// A CG iteration's third Dslash does not need alpha, the fourth does: the
+// first blocks of the third one's grid form it from the second one's partials
+// beside the Dslash blocks, which saves the launch (4 to 5 us) of a kernel of
+// its own.  A slot that this finds numerically dead goes on as dead; whether a
+// block of this launch still saw it running does not matter, the next skips it.
+template <int EPI, bool SLOT>
+__device__ __forceinline__ bool alpha_block(const DslashArgs &A)
+{
+    if constexpr (EPI == EPI_PLAIN && SLOT) {
+        const int b = (int)blockIdx.x;
+        if (b >= A.alpha_blocks) return false;
+        if (b < A.nslot && threadIdx.x < 64) cg_alpha_wave(A.st[b], A.partial + (size_t)b * A.ntile, A.ntile);
+        return true;
+    }
+    return false;
+}
+
 struct WalkPos {
     int buf;     // LDS buffer holding the current timeslice
     int l;       // the thread's site within the chunk (idle lanes: the last one)
@@ -918,7 +935,10 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
     __shared__ WalkBuf<SP> W;
     int sb, slot;
     constexpr bool BOTH = EPI == EPI_PLAIN && !SLOT && SRC == 0;
-    if (!map_block(BOTH && A0.par_bytes ? 2 * A0.nblk_site : A0.nblk_site, A0.nslot, A0.swz, sb, slot, A0.gouter != 0))
+    if (alpha_block<EPI, SLOT>(A0)) return;
+    const int first = EPI == EPI_PLAIN && SLOT ? A0.alpha_blocks : 0;
+    if (!map_block(BOTH && A0.par_bytes ? 2 * A0.nblk_site : A0.nblk_site, A0.nslot, A0.swz, sb, slot, A0.gouter != 0,
+                   first))
         return;
     DslashArgs A = A0;
     if constexpr (BOTH) sb = pick_parity(A, sb);
@@ -1090,7 +1110,10 @@ __global__ __launch_bounds__(512, (SP == P64 ? 2 : 4)) void k_dslash_split(const
     __shared__ cpx<T> half[8][6][64];
     int tile, slot;
     constexpr bool BOTH = EPI == EPI_PLAIN && !SLOT && SRC == 0;
-    if (!map_block(BOTH && A0.par_bytes ? 2 * A0.nblk_site : A0.nblk_site, A0.nslot, A0.swz, tile, slot)) return;
+    if (alpha_block<EPI, SLOT>(A0)) return;
+    const int first = EPI == EPI_PLAIN && SLOT ? A0.alpha_blocks : 0;
+    if (!map_block(BOTH && A0.par_bytes ? 2 * A0.nblk_site : A0.nblk_site, A0.nslot, A0.swz, tile, slot, false, first))
+        return;
     DslashArgs A = A0;
     if constexpr (BOTH) tile = pick_parity(A, tile);
     double kappa = A.kappa_u, a = A.a_u, alpha = 0;
@@ -1257,7 +1280,8 @@ static bool launch_walk(DslashArgs A, hipStream_t s)
             A.in_span = (uint32_t)field;
             A.gauge_span = (uint32_t)std::min<uint64_t>((uint64_t)2 * 4 * A.g.vh * link_bytes(SP), 0xFFFFFFFFull);
             A.nblk_site = A.ntile = plan.tiles;
-            const int total = plan.tiles * A.nslot * npar, grid = A.swz ? 8 * ((total + 7) / 8) : total;
+            const int total = plan.tiles * A.nslot * npar;
+            const int grid = A.alpha_blocks + (A.swz ? 8 * ((total + 7) / 8) : total);
             if (A.st) hipLaunchKernelGGL((k_dslash_split<SP, DAG, EPI, IN2, PO == SP && SRC == 0, SRC, PO>), dim3(grid), dim3(512), 0, s, A);
             else hipLaunchKernelGGL((k_dslash_split<SP, DAG, EPI, IN2, false, SRC, PO>), dim3(grid), dim3(512), 0, s, A);
             return true;
@@ -1272,7 +1296,7 @@ static bool launch_walk(DslashArgs A, hipStream_t s)
         A.nblk_site = plan.chunks * (A.g.L[3] / tw);
         A.ntile = plan.tiles;
         const int total = A.nblk_site * A.nslot * npar;
-        const int grid = A.swz ? 8 * ((total + 7) / 8) : total;
+        const int grid = A.alpha_blocks + (A.swz ? 8 * ((total + 7) / 8) : total);
         const bool part = plan.cy * plan.cz * A.g.lxh != plan.threads;
         // outputs are streamed past the caches (non-temporal), which keeps L2 for
         // the halo lines, except FP32 ones that the next kernel can find in the

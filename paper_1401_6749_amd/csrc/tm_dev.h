@@ -482,16 +482,51 @@ __device__ __forceinline__ double block_sum(double v, double *lds /* NT/64 doubl
     return v;
 }
 
+// ---------------------------------------------------------------------------
+// alpha of a CG slot, by one wave: <p, Ap> from n partials in a fixed order
+// (lane l adds v[l + 64 (8 k + j)] in eight running sums j, then the eight in
+// pairs, then the wave) and the step that alpha owes to x.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ bool finite_pos(double v) { return v > 0.0 && v < 1.0e300; }
+
+__device__ __forceinline__ void cg_alpha_wave(SlotState &S, const double *v, int n)
+{
+    const int lane = (int)threadIdx.x & 63;
+    if (S.status != ST_RUNNING) {
+        if (lane == 0) S.xpend = 0;  // no step this iteration
+        return;
+    }
+    double s[8];
+#pragma unroll
+    for (int j = 0; j < 8; j++) s[j] = 0.0;
+    for (int i0 = lane; i0 < n; i0 += 8 * 64)
+#pragma unroll
+        for (int j = 0; j < 8; j++)
+            if (i0 + 64 * j < n) s[j] += v[i0 + 64 * j];
+    const double pap = wave_sum(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])));
+    if (lane != 0) return;
+    S.pap = pap;
+    if (!finite_pos(pap)) {
+        S.status = ST_NUMERIC;
+        S.alpha = 0.0;
+        S.xpend = 0;
+    } else {
+        S.alpha = S.rr / pap;
+        S.xpend = 1;
+    }
+}
+
 // XCD-aware block mapping.  Consecutive hardware block ids are dealt out to
 // the 8 XCDs in turn; remap so that each XCD walks a contiguous range of
 // (site block, slot) pairs, slots of the same site block back to back, so
 // the links and neighbour spinors of a range stay in that XCD's L2.
 // gouter: slot (group) index slowest instead of fastest
+// first: blocks of the grid before these (a multiple of 8)
 __device__ __forceinline__ bool map_block(int nblk_site, int nslot, int swz, int &sblk, int &slot,
-                                          bool gouter = false)
+                                          bool gouter = false, int first = 0)
 {
     const int total = nblk_site * nslot;
-    const int bid = blockIdx.x;
+    const int bid = (int)blockIdx.x - first;
     int l = bid;
     if (swz) {
         const int per = (total + 7) >> 3;

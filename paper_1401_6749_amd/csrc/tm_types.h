@@ -145,6 +145,8 @@ struct DslashArgs {
     int wcy, wcz;                  // timeslice-walk chunk: y rows x z planes of full x rows (set by the launcher)
     int keep;                      // FP32 plain and norm epilogues store through the caches (set by the launcher)
     double *partial;            // [nslot][ntile]
+    int alpha_blocks;           // plain epilogue with slots: blocks before the others, block i < nslot forming
+                                // slot i's alpha from partial (a multiple of 8; 0: none)
     // EPI_CGUPD (r), EPI_START (x, r)
     char *x, *r;
     const char *p;
