@@ -171,6 +171,25 @@ struct RawZ4 {
     }
 };
 
+// an FP32 link as stored (rows 0 and 1), to be loaded ahead of its use
+struct LinkRaw {
+    float4 q[3];
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, int vh, int pm, int i)
+    {
+#pragma unroll
+        for (int g = 0; g < 3; g++) q[g] = as_f4(bld16(rs, (uint32_t)i * 16u, ((uint32_t)pm * 3u + g) * (uint32_t)vh * 16u));
+    }
+    __device__ __forceinline__ void get(Link<float> &L) const
+    {
+#pragma unroll
+        for (int g = 0; g < 3; g++) {
+            L.u[(2 * g) / 3][(2 * g) % 3] = cpx<float>{q[g].x, q[g].y};
+            L.u[(2 * g + 1) / 3][(2 * g + 1) % 3] = cpx<float>{q[g].z, q[g].w};
+        }
+        rebuild_row2(L);
+    }
+};
+
 // link (par, mu) of site i through the gauge resource
 template <int SP, class T>
 __device__ __forceinline__ void load_link(__amdgpu_buffer_rsrc_t rs, int vh, int par, int mu, int i, Link<T> &L)
@@ -435,6 +454,10 @@ __device__ __forceinline__ void hop_w_pk(const DslashArgs &A, __amdgpu_buffer_rs
     for (int a = 0; a < 3; a++) w[3 + a] = cpx<float>{wr[a], wi[a]};
 }
 
+template <class T, int MU, bool FWD, bool DAG, class RawT>
+__device__ __forceinline__ void hop_w_link(const DslashArgs &A, const Site &s, const Link<T> &L, const RawT &raw,
+                                           cpx<T> w[6]);
+
 // The two transported spin rows of neighbour n of site s before they are added into the output spinor: the projector, the link
 // product and the antiperiodic sign of a temporal hop that wraps.  For the
 // backward t neighbour only s.t is read.
@@ -446,9 +469,15 @@ __device__ __forceinline__ void hop_w(const DslashArgs &A, __amdgpu_buffer_rsrc_
         hop_w_pk<SP, MU, FWD, DAG>(A, gauge, s, n, raw, w);
         return;
     }
-    constexpr int S = (FWD != DAG) ? -1 : 1;
     Link<T> L;
     load_link<SP, T>(gauge, A.g.vh, FWD ? A.out_par : 1 - A.out_par, MU, FWD ? s.cb : n, L);
+    hop_w_link<T, MU, FWD, DAG, RawT>(A, s, L, raw, w);
+}
+template <class T, int MU, bool FWD, bool DAG, class RawT>
+__device__ __forceinline__ void hop_w_link(const DslashArgs &A, const Site &s, const Link<T> &L, const RawT &raw,
+                                           cpx<T> w[6])
+{
+    constexpr int S = (FWD != DAG) ? -1 : 1;
     transport<T, MU, S, FWD>(L, raw, w);
     if (MU == 3 && A.g.tbc < 0 && s.t == (FWD ? A.g.L[3] - 1 : 0)) {
 #pragma unroll
@@ -856,10 +885,17 @@ struct WalkPos {
 // done, t+1 after).
 // y/z neighbours outside the chunk come from the prefetched halo (hy, hz)
 // when there is one, else from global memory.
-template <int SP, int MU, bool FWD, bool DAG, class RawT>
+// FP32 takes its link from link, loaded a stage ahead, and starts the next
+// stage's with fetch() once its own neighbour is on the way (loads come back
+// in order).
+struct NoFetch {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <int SP, int MU, bool FWD, bool DAG, class RawT, class Fetch = NoFetch>
 __device__ __forceinline__ void walk_dir(const DslashArgs &A, const HopRes &R, const Site &s, const WalkBuf<SP> &W,
                                          const WalkPos &w, cpx<typename Real<SP>::T> acc[12], const RawT &hy,
-                                         const RawT &hz, int pf)
+                                         const RawT &hz, int pf, const LinkRaw *link = nullptr,
+                                         const Fetch &fetch = Fetch())
 {
     using T = typename Real<SP>::T;
     const int n = nbr<MU, FWD ? 1 : -1>(A.g, s);
@@ -885,7 +921,16 @@ __device__ __forceinline__ void walk_dir(const DslashArgs &A, const HopRes &R, c
         else if (MU == 1 && (pf & 2)) raw = hy;
         else if (MU == 2 && (pf & 1)) raw = hz;
         else raw.load(R.in, 0, A.g.vh, n);
-        hop_compute<T, SP, MU, FWD, DAG, RawT>(A, R.gauge, s, n, raw, acc);
+        if constexpr (SP == P32) {
+            fetch();
+            Link<T> L;
+            link->get(L);
+            cpx<T> v[6];
+            hop_w_link<T, MU, FWD, DAG, RawT>(A, s, L, raw, v);
+            accum<T, MU, (FWD != DAG) ? -1 : 1>(acc, v);
+        } else {
+            hop_compute<T, SP, MU, FWD, DAG, RawT>(A, R.gauge, s, n, raw, acc);
+        }
     }
 }
 
@@ -1001,6 +1046,8 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
             W.put(0, l, r1);
         }
     }
+    LinkRaw link;
+    if constexpr (SP == P32) link.load(R.gauge, vh, A.out_par * 4, t0 * g.st + o);
     __syncthreads();
     for (int k = 0; k < tw; k++) {
         const int t = t0 + k;
@@ -1016,21 +1063,44 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
             // the neighbours in the same order as with two buffers: backward
             // t (carried), x, y, z, forward t (nxt, still in registers)
             accum<T, 3, SB>(acc, carry);
+            // FP32: the link of the next stage is loaded a stage ahead, in registers
+            // that FP64 and half precision do not have (153 to 161 of 168, 143 to 153
+            // before).  Mhat at 16^3x32, 1 / 4 / 12 right-hand sides: 20.6 / 44.9 /
+            // 96.8 -> 18.0 / 41.2 / 93.5 us; hop of 12 at 32^3x64, both parities, 1665
+            // -> 1625 us
+            LinkRaw ahead;
+#define TMK_STAGE(MU, FWD, NMU, NFWD)                                                                             \
+    walk_dir<SP, MU, FWD, DAG>(A, R, s, W, w, acc, hy, hz, pf, &link, [&]() {                                     \
+        ahead.load(R.gauge, vh, (NFWD ? A.out_par : 1 - A.out_par) * 4 + NMU, NFWD ? cb : nbr<NMU, -1>(g, s));    \
+    });
 #pragma unroll 1
             for (int d = 0; d < 6; d++) {
                 switch (__builtin_amdgcn_readfirstlane(d)) {
-                case 0: walk_dir<SP, 0, true, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
-                case 1: walk_dir<SP, 0, false, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
-                case 2: walk_dir<SP, 1, true, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
-                case 3: walk_dir<SP, 1, false, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
-                case 4: walk_dir<SP, 2, true, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
-                default: walk_dir<SP, 2, false, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
+                case 0: TMK_STAGE(0, true, 0, false) break;
+                case 1: TMK_STAGE(0, false, 1, true) break;
+                case 2: TMK_STAGE(1, true, 1, false) break;
+                case 3: TMK_STAGE(1, false, 2, true) break;
+                case 4: TMK_STAGE(2, true, 2, false) break;
+                default: TMK_STAGE(2, false, 3, true) break;
                 }
+                if constexpr (SP == P32) link = ahead;
             }
+#undef TMK_STAGE
             // the thread's own site of t+1, loaded only now so that it is not
             // held in registers through the spatial neighbours
             nxt.load(R.in, 0, vh, ((t + 1) % lt) * g.st + o);
-            hop_compute<T, SP, 3, true, DAG, RawT>(A, R.gauge, s, nbr<3, 1>(g, s), nxt, acc);
+            if constexpr (SP == P32) {
+                // backward t link of the next output, then its first link
+                if (k + 1 < tw) ahead.load(R.gauge, vh, (1 - A.out_par) * 4 + 3, cb);
+                Link<T> L;
+                link.get(L);
+                if (k + 1 < tw) link.load(R.gauge, vh, A.out_par * 4, cb + g.st);
+                cpx<T> v[6];
+                hop_w_link<T, 3, true, DAG, RawT>(A, s, L, nxt, v);
+                accum<T, 3, DAG ? 1 : -1>(acc, v);
+            } else {
+                hop_compute<T, SP, 3, true, DAG, RawT>(A, R.gauge, s, nbr<3, 1>(g, s), nxt, acc);
+            }
             if (k + 1 < tw) {
                 __syncthreads();  // every read of timeslice t is done
                 // only this thread writes its slot: its own site of t (the
@@ -1042,7 +1112,13 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
                 if (live) W.put(0, l, nxt);
                 Site s1 = s;
                 s1.t = t + 1 == lt ? 0 : t + 1;
-                hop_w<T, SP, 3, false, DAG, RawT>(A, R.gauge, s1, cb, own, carry);
+                if constexpr (SP == P32) {
+                    Link<T> L;
+                    ahead.get(L);
+                    hop_w_link<T, 3, false, DAG, RawT>(A, s1, L, own, carry);
+                } else {
+                    hop_w<T, SP, 3, false, DAG, RawT>(A, R.gauge, s1, cb, own, carry);
+                }
             }
         } else {
             // backward t neighbour first: it frees this thread's slot of
