@@ -81,6 +81,10 @@ def code_text(src: str) -> str:
     return " ".join("".join(out).split())
 
 
+# output parities that one launch of a full-lattice operator covers
+PARITIES = 2
+
+
 def kernel_hash() -> str:
     h = hashlib.sha256()
     for f in KERNEL_SOURCES:
@@ -131,7 +135,7 @@ def measure_roofline(torch, tm, inputs, ctx, g, W, workload):
     n_calls = 20
     t_call = event_time(torch, lambda: tm.tm_dslash_ex(ctx, g, "hop", W["kappa"], W["a"], prec, nrhs, fin, pitch,
                                                         fout, pitch), n_calls)
-    t_launch = t_call / 2  # one launch per output parity
+    t_launch = t_call / PARITIES  # figures per output parity
     alg_bytes = vh * (8 * LINK_BYTES[prec] + nrhs * 2 * SPINOR_BYTES[prec])
     storage_bytes = vh * (8 * LINK_STORAGE_BYTES[prec] + nrhs * 2 * SPINOR_BYTES[prec])
     achieved = alg_bytes / t_launch / 1e9
@@ -153,7 +157,7 @@ def measure_roofline(torch, tm, inputs, ctx, g, W, workload):
     return {
         "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-        "kernel": f"k_dslash_walk {prec} hop, {nrhs} RHS per launch, {dims[0]}^3x{dims[3]}",
+        "kernel": f"k_dslash_walk {prec} hop, {nrhs} RHS per launch, {dims[0]}^3x{dims[3]}, per output parity",
         "alg_bytes_per_launch": alg_bytes,
         "alg_bytes_per_site": 8 * LINK_BYTES[prec] + nrhs * 2 * SPINOR_BYTES[prec],
         "storage_bytes_per_launch": storage_bytes,
@@ -180,7 +184,7 @@ def kernel_rates(torch, tm, inputs, ctx, g, W):
             tm.tm_field_import(ctx, g, prec, 1, psi, fin[r * pitch:r * pitch + fb])
         fout = torch.zeros_like(fin)
         t = event_time(torch, lambda: tm.tm_dslash_ex(ctx, g, "hop", W["kappa"], W["a"], prec, nrhs, fin, pitch,
-                                                       fout, pitch), 10) / 2
+                                                       fout, pitch), 10) / PARITIES
         alg = vh * (8 * LINK_BYTES[prec] + nrhs * 2 * SPINOR_BYTES[prec])
         sto = vh * (8 * LINK_STORAGE_BYTES[prec] + nrhs * 2 * SPINOR_BYTES[prec])
         out.append({"prec": prec, "nrhs": nrhs, "launch_us": round(t * 1e6, 1), "alg_GBs": round(alg / t / 1e9, 1),
@@ -352,10 +356,11 @@ def cpu_model() -> str:
     return "unknown"
 
 
-def write_traffic(fetch_db: str, write_db: str, workload: str) -> None:
-    """Per-launch HBM bytes of the roofline kernel from FETCH_SIZE and
-    WRITE_SIZE (KiB per dispatch), each scaled by what the same counter reads
-    for the 1 GiB streaming copy (which reads and writes exactly 1 GiB)."""
+def write_traffic(fetch_db: str, write_db: str, workload: str, parities: int = 1) -> None:
+    """HBM bytes of the roofline kernel per output parity, like every per-launch
+    figure of the bench line, from FETCH_SIZE and WRITE_SIZE (KiB per dispatch
+    of `parities` parities), each scaled by what the same counter reads for
+    the 1 GiB streaming copy (which reads and writes exactly 1 GiB)."""
     import sqlite3
 
     W = WORKLOADS[workload]
@@ -374,11 +379,12 @@ def write_traffic(fetch_db: str, write_db: str, workload: str) -> None:
     cw, kw, nw = per_dispatch(write_db, "WRITE_SIZE")
     f_fetch = (1 << 30) / (cf * 1024.0)
     f_write = (1 << 30) / (cw * 1024.0)
-    fetch = kf * 1024.0 * f_fetch
-    write = kw * 1024.0 * f_write
+    fetch = kf * 1024.0 * f_fetch / parities
+    write = kw * 1024.0 * f_write / parities
     out = {
         "workload": workload, "nrhs": W["batch"], "kernel_hash": kernel_hash(),
-        "kernel": "k_dslash_walk FP16 hop (uniform parameters), one launch per output parity",
+        "kernel": "k_dslash_walk FP16 hop (uniform parameters), bytes per output parity",
+        "parities_per_dispatch": parities,
         "fetch_scale": round(f_fetch, 4), "write_scale": round(f_write, 4),
         "fetch_bytes_per_launch": round(fetch), "write_bytes_per_launch": round(write),
         "hbm_bytes_per_launch": round(fetch + write), "dispatches": [nf, nw],
@@ -867,7 +873,7 @@ def main():
         print(txt, end="")
         return
     if args.traffic_from:
-        write_traffic(args.traffic_from[0], args.traffic_from[1], args.workload)
+        write_traffic(args.traffic_from[0], args.traffic_from[1], args.workload, PARITIES)
         return
     if args.counter_summary:
         if len(args.counter_summary) < 4:
@@ -878,8 +884,8 @@ def main():
         b = "--" + mode
         Wc = WORKLOADS[args.workload]
         d0, d1, d2, d3 = Wc["dims"]
-        # a contraction dispatch covers the whole lattice, a hop dispatch one parity
-        sites = d0 * d1 * d2 * d3 // (2 if mode == "roofline-only" else 1)
+        # a contraction dispatch covers the whole lattice, a hop dispatch PARITIES of its two parities
+        sites = d0 * d1 * d2 * d3 * (PARITIES if mode == "roofline-only" else 2) // 2
         counter_summary(o, k, b, args.counter_summary[3:], sites=sites, sources=Wc["batch"])
         return
     if args.gpus != 1:

@@ -871,33 +871,23 @@ struct WalkPos {
     int yy, zz;  // its row and plane within the chunk
 };
 
-// Halo prefetch of the half-precision walk (bit 0: z halo, bit 1: y halo):
-// a thread on the chunk's edge loads its neighbour outside the chunk for the
-// next timeslice at the end of a step, when the block owning that
-// neighbour has just fetched it (its own next timeslice), instead of one
-// step later, when the L2 has usually dropped the line.
-#ifndef TM_WALK_HALO_PF
-#define TM_WALK_HALO_PF 0
-#endif
-
 // t neighbours (two-buffer walk only): this thread's own site in timeslices
 // t+-1, both in the other LDS buffer (t-1 until the backward neighbour is
 // done, t+1 after).
-// y/z neighbours outside the chunk come from the prefetched halo (hy, hz)
-// when there is one, else from global memory.
+// y/z neighbours outside the chunk come from global memory.
 // FP32 takes its link from link, loaded a stage ahead, and starts the next
 // stage's with fetch() once its own neighbour is on the way (loads come back
 // in order).
 struct NoFetch {
     __device__ __forceinline__ void operator()() const {}
 };
-template <int SP, int MU, bool FWD, bool DAG, class RawT, class Fetch = NoFetch>
+template <int SP, int MU, bool FWD, bool DAG, class Fetch = NoFetch>
 __device__ __forceinline__ void walk_dir(const DslashArgs &A, const HopRes &R, const Site &s, const WalkBuf<SP> &W,
-                                         const WalkPos &w, cpx<typename Real<SP>::T> acc[12], const RawT &hy,
-                                         const RawT &hz, int pf, const LinkRaw *link = nullptr,
-                                         const Fetch &fetch = Fetch())
+                                         const WalkPos &w, cpx<typename Real<SP>::T> acc[12],
+                                         const LinkRaw *link = nullptr, const Fetch &fetch = Fetch())
 {
     using T = typename Real<SP>::T;
+    using RawT = typename RawSel<SP, T>::type;
     const int n = nbr<MU, FWD ? 1 : -1>(A.g, s);
     if constexpr (MU == 3) {
         RawT raw;
@@ -918,8 +908,6 @@ __device__ __forceinline__ void walk_dir(const DslashArgs &A, const HopRes &R, c
             d = l + (q - (MU == 1 ? w.yy : w.zz)) * (MU == 1 ? A.g.lxh : A.g.lxh * A.wcy);
         }
         if (in) W.get(w.buf, d, raw);
-        else if (MU == 1 && (pf & 2)) raw = hy;
-        else if (MU == 2 && (pf & 1)) raw = hz;
         else raw.load(R.in, 0, A.g.vh, n);
         if constexpr (SP == P32) {
             fetch();
@@ -1011,23 +999,6 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
     R.gauge = mkrsrc(A.gauge, A.gauge_span);
     R.in = mkrsrc(A.in + (size_t)slot * A.in_slot, A.in_span);
     R.lane = 0;
-    // halo prefetch roles: the one y (z) neighbour of this thread outside the
-    // chunk, if the chunk is at least two rows (planes) deep and does not
-    // span the dimension; pf bit set only for threads that have one
-    constexpr int PF = (SP == P16 || SP == PBF) ? TM_WALK_HALO_PF : 0;
-    int ydir = 0, zdir = 0, pf = 0;
-    if constexpr ((PF & 2) != 0)
-        if (A.wcy >= 2 && A.wcy < g.L[1]) ydir = yy == 0 ? -1 : (yy == A.wcy - 1 ? 1 : 0);
-    if constexpr ((PF & 1) != 0)
-        if (A.wcz >= 2 && A.wcz < g.L[2]) zdir = zz == 0 ? -1 : (zz == A.wcz - 1 ? 1 : 0);
-    pf = (ydir ? 2 : 0) | (zdir ? 1 : 0);
-    RawT hy{}, hz{};
-    // halo sites of timeslice t (same o) into hy / hz
-    auto halo_load = [&](int t) {
-        const Site s1 = site_of(g, t * g.st + o, A.out_par);
-        if (ydir) hy.load(R.in, 0, vh, ydir > 0 ? nbr<1, 1>(g, s1) : nbr<1, -1>(g, s1));
-        if (zdir) hz.load(R.in, 0, vh, zdir > 0 ? nbr<2, 1>(g, s1) : nbr<2, -1>(g, s1));
-    };
     constexpr int NB = walk_nbuf<SP>();
     // the backward t neighbour's projector sign (FWD = false)
     constexpr int SB = DAG ? -1 : 1;
@@ -1036,7 +1007,6 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
         RawT r0, r1;
         r0.load(R.in, 0, vh, ((t0 + lt - 1) % lt) * g.st + o);
         r1.load(R.in, 0, vh, t0 * g.st + o);
-        if constexpr (PF != 0) halo_load(t0);
         if constexpr (NB == 1) {
             const Site s0 = site_of(g, t0 * g.st + o, A.out_par);
             hop_w<T, SP, 3, false, DAG, RawT>(A, R.gauge, s0, ((t0 + lt - 1) % lt) * g.st + o, r0, carry);
@@ -1070,7 +1040,7 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
             // -> 1625 us
             LinkRaw ahead;
 #define TMK_STAGE(MU, FWD, NMU, NFWD)                                                                             \
-    walk_dir<SP, MU, FWD, DAG>(A, R, s, W, w, acc, hy, hz, pf, &link, [&]() {                                     \
+    walk_dir<SP, MU, FWD, DAG>(A, R, s, W, w, acc, &link, [&]() {                                     \
         ahead.load(R.gauge, vh, (NFWD ? A.out_par : 1 - A.out_par) * 4 + NMU, NFWD ? cb : nbr<NMU, -1>(g, s));    \
     });
 #pragma unroll 1
@@ -1125,24 +1095,21 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
             // timeslice t-1, which then takes timeslice t+1 (the forward t
             // neighbour now and the next step's spatial neighbours), so nxt is
             // not held in registers through the other seven neighbours.
-            walk_dir<SP, 3, false, DAG>(A, R, s, W, w, acc, hy, hz, pf);
+            walk_dir<SP, 3, false, DAG>(A, R, s, W, w, acc);
             if (live) W.put(w.buf ^ 1, l, nxt);
 #pragma unroll 1
             for (int d = 0; d < 7; d++) {
                 switch (__builtin_amdgcn_readfirstlane(d)) {
-                case 0: walk_dir<SP, 0, true, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
-                case 1: walk_dir<SP, 0, false, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
-                case 2: walk_dir<SP, 1, true, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
-                case 3: walk_dir<SP, 1, false, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
-                case 4: walk_dir<SP, 2, true, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
-                case 5: walk_dir<SP, 2, false, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
-                default: walk_dir<SP, 3, true, DAG>(A, R, s, W, w, acc, hy, hz, pf); break;
+                case 0: walk_dir<SP, 0, true, DAG>(A, R, s, W, w, acc); break;
+                case 1: walk_dir<SP, 0, false, DAG>(A, R, s, W, w, acc); break;
+                case 2: walk_dir<SP, 1, true, DAG>(A, R, s, W, w, acc); break;
+                case 3: walk_dir<SP, 1, false, DAG>(A, R, s, W, w, acc); break;
+                case 4: walk_dir<SP, 2, true, DAG>(A, R, s, W, w, acc); break;
+                case 5: walk_dir<SP, 2, false, DAG>(A, R, s, W, w, acc); break;
+                default: walk_dir<SP, 3, true, DAG>(A, R, s, W, w, acc); break;
                 }
             }
         }
-        // next timeslice's halo, while its owners are reading it
-        if constexpr (PF != 0)
-            if (k + 1 < tw) halo_load(t + 1);
         double part = 0.0;
         if (live) part = epilogue<SP, EPI, IN2, SRC, NT, PO>(A, slot, cb, acc, kappa, a, alpha);
         if constexpr (EPI != EPI_PLAIN) {
