@@ -269,7 +269,8 @@ struct Sched {
         }
         R->remaining = n_hp + n_lpt;
         R->state = RQ_RUNNING;
-        R->t_admit = now;
+        // a request may arrive after the clock was read for this pass
+        R->t_admit = std::max(now, R->t_submit);
         return TM_OK;
     }
 
@@ -279,7 +280,7 @@ struct Sched {
         if (R->dbuf) arena.release(R->dbuf);
         R->dbuf = nullptr;
         R->state = RQ_DONE;
-        R->t_done = now;
+        R->t_done = std::max(now, std::max(R->t_submit, R->t_admit));
         auto it = std::find(active.begin(), active.end(), R);
         if (it != active.end()) active.erase(it);
         {
