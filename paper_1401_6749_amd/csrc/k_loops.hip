@@ -202,23 +202,35 @@ __device__ __forceinline__ void umul_chain(const Link<T> &L, const cpx<T> h[3], 
 // antiperiodic sign of a hop across the time boundary multiplies the noise:
 // for codes it flips their 24 sign bits (the code itself), for a field it
 // multiplies the transported vector.
-// The signs come from an LDS table: entry e < 16 holds the four values of
-// code bits e (for FP64 their high words), entry 16 + e the zeros of flagged
-// sites.  The kernel is bound by vector issue, and a shift and an insert per
-// value were 46 of a kind's 533 vector instructions per site; the six reads
-// take 12, and since the entries lie on different banks they never conflict.
-// 12 FP32 sources at 24^3x48 951 -> 924 us, three FP64 ones at 16^3x32 (with
-// the fields read through global instead of flat loads) 88.8 -> 85.7 us.
-constexpr int Z4_ENTRIES = 32;
+// The signs come from an LDS table of the values of four code bits, then the
+// zeros of flagged sites.  FP32: 16-byte entry e holds the four values of bits
+// e.  FP64: entry e the first two, entry 16 + e the other two.  The kernel is
+// bound by vector issue, and a shift and an insert per value (in FP64 also the
+// zero low words) were 46 of a kind's 533 vector instructions per site; the
+// reads take 12, and since the entries of a half lie on different banks they
+// never conflict.  12 FP32 sources at 24^3x48 951 -> 922 us; FP64, three at
+// 16^3x32 88.8 -> 85.7 us (with the fields read through global instead of flat
+// loads), and the whole doubles of the table against high words only: 12 at
+// 16^3x32 300.7 -> 295.2 us, six at 24^3x48 791 -> 781 us, three unchanged.
+template <int SPS>
+constexpr int z4_entries()
+{
+    return SPS == P64 ? 64 : 32;
+}
 
 template <int SPS>
 __device__ __forceinline__ void z4_table_fill(uint4 *tab)
 {
-    const uint32_t e = threadIdx.x;
-    if (e < Z4_ENTRIES) {
-        const uint32_t one_hi = e >= 16 ? 0u : SPS == P64 ? 0x3FF00000u : 0x3F800000u;
-        tab[e] = make_uint4(one_hi | (e << 31), one_hi | (e >> 1 << 31), one_hi | (e >> 2 << 31),
-                            one_hi | (e >> 3 << 31));
+    const uint32_t i = threadIdx.x;
+    if (i < z4_entries<SPS>()) {
+        const bool zero = i >= z4_entries<SPS>() / 2;
+        if constexpr (SPS == P64) {
+            const uint32_t one = zero ? 0u : 0x3FF00000u, e = (i & 15) >> (i & 16 ? 2 : 0);
+            tab[i] = make_uint4(0u, one | (e << 31), 0u, one | (e >> 1 << 31));
+        } else {
+            const uint32_t one = zero ? 0u : 0x3F800000u;
+            tab[i] = make_uint4(one | (i << 31), one | (i >> 1 << 31), one | (i >> 2 << 31), one | (i >> 3 << 31));
+        }
     }
     __syncthreads();
 }
@@ -228,12 +240,6 @@ struct LeftVec {
     const uint32_t *codes;
     const char *fld[2];
     const uint4 *tab;  // z4_table_fill
-    template <class T>
-    __device__ static __forceinline__ T z4_part(uint32_t hi)
-    {
-        if constexpr (sizeof(T) == 8) return __hiloint2double((int)hi, 0);
-        else return __uint_as_float(hi);
-    }
     // unscaled Z4 values: (+-1, +-1), (0, 0) at flagged sites
     template <class T>
     __device__ __forceinline__ void get(const Geom &g, int par, int cb, cpx<T> l[12], bool neg = false) const
@@ -243,14 +249,22 @@ struct LeftVec {
         } else {
             uint32_t c = codes[(size_t)par * g.vh + cb];
             if (neg) c ^= 0x00FFFFFFu;
-            const uint32_t base = (c >> 23) & 0x100u;  // Z4_ZERO, bit 31: byte offset of entry 16
-            static_assert(Z4_ZERO == 0x80000000u, "the flag selects the upper half of the table");
+            // byte offset of the zeros at flagged sites
+            const uint32_t base = (c >> (SPS == P64 ? 22 : 23)) & (8u * z4_entries<SPS>());
+            static_assert(Z4_ZERO == 0x80000000u, "bit 31 selects the upper half of the table");
 #pragma unroll
             for (int m = 0; m < 6; m++) {
                 const uint32_t off = ((m == 0 ? c << 4 : c >> (4 * m - 4)) & 0xF0u) | base;
-                const uint4 w = *(const uint4 *)((const char *)tab + off);
-                l[2 * m] = cpx<T>{z4_part<T>(w.x), z4_part<T>(w.y)};
-                l[2 * m + 1] = cpx<T>{z4_part<T>(w.z), z4_part<T>(w.w)};
+                const uint4 *e = (const uint4 *)((const char *)tab + off);
+                if constexpr (SPS == P64) {
+                    const double2 v = *(const double2 *)e, w = *(const double2 *)(e + 16);
+                    l[2 * m] = cpx<T>{v.x, v.y};
+                    l[2 * m + 1] = cpx<T>{w.x, w.y};
+                } else {
+                    const float4 v = *(const float4 *)e;
+                    l[2 * m] = cpx<T>{v.x, v.y};
+                    l[2 * m + 1] = cpx<T>{v.z, v.w};
+                }
             }
         }
     }
@@ -375,7 +389,7 @@ void k_contract(Geom g, const void *G, const char *s_even, const char *s_odd, si
     const int i = l % n, tc = l / n;
     const int t = tc / nchunk, chunk = tc - t * nchunk;
     const char *s_fld[2] = {s_even + (size_t)i * s_stride, s_odd + (size_t)i * s_stride};
-    __shared__ uint4 z4_tab[FIELD ? 1 : Z4_ENTRIES];
+    __shared__ uint4 z4_tab[FIELD ? 1 : z4_entries<SPS>()];
     if constexpr (!FIELD) z4_table_fill<SPS>(z4_tab);
     LeftVec<SPS, FIELD> left;
     left.tab = z4_tab;
