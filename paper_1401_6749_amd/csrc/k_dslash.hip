@@ -767,9 +767,11 @@ __global__ __launch_bounds__(BLOCK, dslash_waves<SP>()) void k_dslash(const Dsla
 // below, and y rows at the chunk's edges) are read from global memory, where
 // the blocks working on those chunks have just fetched them into L2.  The
 // chunk shape is picked on the host (walk_plan); each wave is one reduction
-// tile.  The arithmetic per neighbour is
-// that of k_dslash, in the same order (backward t first, forward t last), so
-// both buffer schemes give the same bits.
+// tile.  The arithmetic per neighbour is that of k_dslash.  The neighbours are
+// added backward t first and forward t last (k_dslash adds both t neighbours
+// last), so both buffer schemes give the same bits; in half precision, where
+// the order shows, lattices under both_t_last keep k_dslash's order (TL; 12 FP16
+// solves of 7 iterations at 24^3x48 take 16.1 ms either way).
 // ---------------------------------------------------------------------------
 // LDS buffers per block: one timeslice or two.  With two, the thread's own
 // site of t+1 goes into the second buffer while the block still reads
@@ -960,7 +962,9 @@ __device__ __forceinline__ int pick_parity(DslashArgs &A, int sb)
 // PART: the chunk's last wave is partly filled; its lanes beyond the last site
 // follow that site and write nothing (a variant of its own, because the masks
 // cost the full chunks 1.5% of the 12-RHS FP16 hop).
-template <int SP, bool DAG, int EPI, bool IN2, bool SLOT, bool NT, int SRC = 0, int PO = SP, bool PART = false>
+// TL: half precision with both t neighbours last (both_t_last).
+template <int SP, bool DAG, int EPI, bool IN2, bool SLOT, bool NT, int SRC = 0, int PO = SP, bool PART = false,
+          bool TL = false>
 __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_walk(const DslashArgs A0)
 {
     using T = typename Real<SP>::T;
@@ -1023,7 +1027,7 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
         const int t = t0 + k;
         const int cb = t * g.st + o;
         RawT nxt;
-        if constexpr (NB != 1) nxt.load(R.in, 0, vh, ((t + 1) % lt) * g.st + o);
+        if constexpr (NB != 1 && !TL) nxt.load(R.in, 0, vh, ((t + 1) % lt) * g.st + o);
         const WalkPos w{NB == 1 ? 0 : (k & 1), l, yy, zz};
         const Site s = site_of(g, cb, A.out_par);
         cpx<T> acc[12];
@@ -1090,6 +1094,28 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
                     hop_w<T, SP, 3, false, DAG, RawT>(A, R.gauge, s1, cb, own, carry);
                 }
             }
+        } else if constexpr (TL) {
+#pragma unroll 1
+            for (int d = 0; d < 6; d++) {
+                switch (__builtin_amdgcn_readfirstlane(d)) {
+                case 0: walk_dir<SP, 0, true, DAG>(A, R, s, W, w, acc); break;
+                case 1: walk_dir<SP, 0, false, DAG>(A, R, s, W, w, acc); break;
+                case 2: walk_dir<SP, 1, true, DAG>(A, R, s, W, w, acc); break;
+                case 3: walk_dir<SP, 1, false, DAG>(A, R, s, W, w, acc); break;
+                case 4: walk_dir<SP, 2, true, DAG>(A, R, s, W, w, acc); break;
+                default: walk_dir<SP, 2, false, DAG>(A, R, s, W, w, acc); break;
+                }
+            }
+            // the backward t neighbour is transported while timeslice t+1 is on
+            // its way, and added after the forward one
+            nxt.load(R.in, 0, vh, ((t + 1) % lt) * g.st + o);
+            RawT own;
+            W.get(w.buf ^ 1, l, own);
+            cpx<T> wb[6];
+            hop_w<T, SP, 3, false, DAG, RawT>(A, R.gauge, s, nbr<3, -1>(g, s), own, wb);
+            hop_compute<T, SP, 3, true, DAG, RawT>(A, R.gauge, s, nbr<3, 1>(g, s), nxt, acc);
+            accum<T, 3, SB>(acc, wb);
+            if (live) W.put(w.buf ^ 1, l, nxt);
         } else {
             // backward t neighbour first: it frees this thread's slot of
             // timeslice t-1, which then takes timeslice t+1 (the forward t
@@ -1132,8 +1158,8 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
 // chunk, the same sites in the same lanes) for one right-hand side: wave d
 // loads neighbour d and its link and transports it, so the eight latencies
 // overlap; the half spinors meet in LDS and wave 0 adds them in the walk's
-// order (backward t, x, y, z, forward t) and runs the epilogue.  Outputs and
-// sums have the walk's bits.
+// order (backward t, x, y, z, forward t; with TL both t last) and runs the
+// epilogue.  Outputs and sums have the walk's bits.
 // ---------------------------------------------------------------------------
 template <class T, int SP, int MU, bool FWD, bool DAG, class RawT>
 __device__ __forceinline__ void split_dir(const DslashArgs &A, const HopRes &R, const Site &s, double den, double a,
@@ -1146,7 +1172,7 @@ __device__ __forceinline__ void split_dir(const DslashArgs &A, const HopRes &R, 
     hop_w<T, SP, MU, FWD, DAG, RawT>(A, R.gauge, s, n, raw, w);
 }
 
-template <int SP, bool DAG, int EPI, bool IN2, bool SLOT, int SRC = 0, int PO = SP>
+template <int SP, bool DAG, int EPI, bool IN2, bool SLOT, int SRC = 0, int PO = SP, bool TL = false>
 __global__ __launch_bounds__(512, (SP == P64 ? 2 : 4)) void k_dslash_split(const DslashArgs A0)
 {
     using T = typename Real<SP>::T;
@@ -1218,7 +1244,7 @@ __global__ __launch_bounds__(512, (SP == P64 ? 2 : 4)) void k_dslash_split(const
     };
     using P = std::integral_constant<int, SF>;
     using M = std::integral_constant<int, -SF>;
-    add(0, std::integral_constant<int, 3>{}, M{});
+    if constexpr (!TL) add(0, std::integral_constant<int, 3>{}, M{});
     add(1, std::integral_constant<int, 0>{}, P{});
     add(2, std::integral_constant<int, 0>{}, M{});
     add(3, std::integral_constant<int, 1>{}, P{});
@@ -1226,6 +1252,7 @@ __global__ __launch_bounds__(512, (SP == P64 ? 2 : 4)) void k_dslash_split(const
     add(5, std::integral_constant<int, 2>{}, P{});
     add(6, std::integral_constant<int, 2>{}, M{});
     add(7, std::integral_constant<int, 3>{}, P{});
+    if constexpr (TL) add(0, std::integral_constant<int, 3>{}, M{});
     double part = 0.0;
     if (live) part = epilogue<SP, EPI, IN2, SRC, false, PO>(A, slot, cb, acc, kappa, a, alpha);
     if constexpr (EPI != EPI_PLAIN) {
@@ -1319,14 +1346,24 @@ static bool launch_walk(DslashArgs A, hipStream_t s)
         A.wcz = plan.cz;
         const int npar = A.par_bytes ? 2 : 1;
         A.par_pairs = A.nslot <= PAIR_MOST;
+        constexpr bool HALF = SP == P16 || SP == PBF;
+        const bool last = HALF && both_t_last(A.g);
         if (plan.tiles * A.nslot * npar <= SPLIT_MOST) {
             A.in_span = (uint32_t)field;
             A.gauge_span = (uint32_t)std::min<uint64_t>((uint64_t)2 * 4 * A.g.vh * link_bytes(SP), 0xFFFFFFFFull);
             A.nblk_site = A.ntile = plan.tiles;
             const int total = plan.tiles * A.nslot * npar;
             const int grid = A.alpha_blocks + (A.swz ? 8 * ((total + 7) / 8) : total);
-            if (A.st) hipLaunchKernelGGL((k_dslash_split<SP, DAG, EPI, IN2, PO == SP && SRC == 0, SRC, PO>), dim3(grid), dim3(512), 0, s, A);
-            else hipLaunchKernelGGL((k_dslash_split<SP, DAG, EPI, IN2, false, SRC, PO>), dim3(grid), dim3(512), 0, s, A);
+            auto split = [&](auto tl) {
+                constexpr bool TL = decltype(tl)::value;
+                if (A.st)
+                    hipLaunchKernelGGL((k_dslash_split<SP, DAG, EPI, IN2, PO == SP && SRC == 0, SRC, PO, TL>), dim3(grid),
+                                       dim3(512), 0, s, A);
+                else
+                    hipLaunchKernelGGL((k_dslash_split<SP, DAG, EPI, IN2, false, SRC, PO, TL>), dim3(grid), dim3(512), 0, s, A);
+            };
+            if (HALF && last) split(std::integral_constant<bool, HALF>{});
+            else split(std::false_type{});
             return true;
         }
         const int tw = walk_length(A.g, plan, A.nslot * npar, walk_waves<SP, EPI>());
@@ -1349,17 +1386,16 @@ static bool launch_walk(DslashArgs A, hipStream_t s)
         // choice at run time costs the large launches 1% for nothing gained.
         const uint64_t written = field * A.nslot * npar;  // bytes
         A.keep = written > (32u << 20) && written <= (128u << 20);
-        auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(plan.threads), 0, s, A); };
-        if constexpr (SRC != 0 || PO != SP) {
-            if (part) go(k_dslash_walk<SP, DAG, EPI, IN2, false, true, SRC, PO, true>);
-            else go(k_dslash_walk<SP, DAG, EPI, IN2, false, true, SRC, PO>);
-        } else if (A.st) {
-            if (part) go(k_dslash_walk<SP, DAG, EPI, IN2, true, true, 0, SP, true>);
-            else go(k_dslash_walk<SP, DAG, EPI, IN2, true, true>);
-        } else {
-            if (part) go(k_dslash_walk<SP, DAG, EPI, IN2, false, true, 0, SP, true>);
-            else go(k_dslash_walk<SP, DAG, EPI, IN2, false, true>);
-        }
+        auto go = [&](auto partly, auto tl) {
+            constexpr bool PART = decltype(partly)::value, TL = decltype(tl)::value;
+            auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(plan.threads), 0, s, A); };
+            if constexpr (SRC != 0 || PO != SP) launch(k_dslash_walk<SP, DAG, EPI, IN2, false, true, SRC, PO, PART, TL>);
+            else if (A.st) launch(k_dslash_walk<SP, DAG, EPI, IN2, true, true, 0, SP, PART, TL>);
+            else launch(k_dslash_walk<SP, DAG, EPI, IN2, false, true, 0, SP, PART, TL>);
+        };
+        using Last = std::integral_constant<bool, HALF>;
+        if (HALF && last) part ? go(std::true_type{}, Last{}) : go(std::false_type{}, Last{});
+        else part ? go(std::true_type{}, std::false_type{}) : go(std::false_type{}, std::false_type{});
         return true;
     }
 }

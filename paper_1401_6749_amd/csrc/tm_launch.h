@@ -62,6 +62,21 @@ inline WalkPlan walk_plan(const Geom &g)
     return p;
 }
 
+// Order of the eight neighbours in half precision: a lattice with a chunk of
+// whole waves on aligned 64-site tiles adds the backward t neighbour first and
+// the forward one last, every other lattice both t neighbours last, as the
+// register kernel does.  The order shows in the low bits of a half-precision
+// spinor (4e-4 of a truncated FP16 solve), so it goes by the lattice alone.
+inline bool both_t_last(const Geom &g)
+{
+    for (int y = 1; y <= g.L[1]; y++)
+        for (int z = 1; g.L[1] % y == 0 && z <= g.L[2]; z++) {
+            const int cs = y * z * g.lxh;
+            if (g.L[2] % z == 0 && cs <= WALK_MAX && cs % 64 == 0 && (y == g.L[1] || (y * g.lxh) % 64 == 0)) return false;
+        }
+    return true;
+}
+
 // Dslash with epilogue; sp = storage precision of in/in2/out/p and of x, r
 // in the CG update (links of the same precision).  Returns -1 on an
 // unsupported combination.
