@@ -42,25 +42,7 @@ __global__ __launch_bounds__(BLOCK) void k_cg_beta(SlotState *st, const double *
     SlotState &S = st[slot];
     if (S.status != ST_RUNNING) return;
     const double rr = sum_fixed(partial + (size_t)slot * nblk, nblk, lds);
-    if (threadIdx.x == 0) {
-        S.iter += 1;
-        S.rr_new = rr;
-        if (!(rr >= 0.0 && rr < 1.0e300)) {
-            S.status = ST_NUMERIC;
-        } else if (S.tol2 > 0.0 && rr <= S.tol2 * S.rr0) {
-            // mixed precision confirms convergence on the true residual
-            S.status = S.mixed ? ST_NEED_UPDATE : ST_CONVERGED;
-            if (!S.mixed) S.rr = rr;
-        } else if (S.mixed && rr <= S.delta2 * S.rr_ref) {
-            S.status = ST_NEED_UPDATE;
-        } else if (S.iter >= S.max_iter) {
-            S.status = ST_MAXITER;
-            S.rr = rr;
-        } else {
-            S.beta = rr / S.rr;
-            S.rr = rr;
-        }
-    }
+    if (threadIdx.x == 0) cg_beta(S, rr);
 }
 
 // block i starts slot st[i] from partial[i*nblk ..]

@@ -658,6 +658,14 @@ __device__ __forceinline__ double epilogue(const DslashArgs &A, int slot, int cb
     return part;
 }
 
+// Whether this Dslash works on a slot: the one with the CG update skips a slot
+// whose curvature broke down, whose status changes at the end of the iteration.
+template <int EPI>
+__device__ __forceinline__ bool slot_runs(const SlotState &st)
+{
+    return EPI == EPI_CGUPD ? cg_steps(st) : st.status == ST_RUNNING;
+}
+
 // Thread mapping: a block holds BLOCK/R sites x R right-hand sides ("slots")
 // of one slot group, lane = site * R + r, so the R lanes of a site sit in the
 // same wave and their link loads hit the same addresses: each link is
@@ -686,15 +694,15 @@ __global__ __launch_bounds__(BLOCK, dslash_waves<SP>()) void k_dslash(const Dsla
 #pragma unroll
         for (int q = 0; q < R; q++) {
             const int sq = grp * R + q;
-            any |= sq < A.nslot && A.st[sq].status == ST_RUNNING;
+            any |= sq < A.nslot && slot_runs<EPI>(A.st[sq]);
         }
         if (!any) return;
         if (live) {
             const SlotState &st = A.st[slot];
-            live = st.status == ST_RUNNING;
+            live = slot_runs<EPI>(st);
             kappa = st.kappa;
             a = st.a;
-            alpha = st.alpha;
+            if (EPI == EPI_CGUPD) alpha = st.alpha;
         }
     }
     const int vh = A.g.vh;
@@ -853,8 +861,9 @@ struct WalkBuf<PBF> : WalkBufHalf<PBF> {};
 // A CG iteration's third Dslash does not need alpha, the fourth does: the
 // first blocks of the third one's grid form it from the second one's partials
 // beside the Dslash blocks, which saves the launch (4 to 5 us) of a kernel of
-// its own.  A slot that this finds numerically dead goes on as dead; whether a
-// block of this launch still saw it running does not matter, the next skips it.
+// its own.  They write alpha, pap and xpend, which no other block of the launch
+// reads, and leave status alone (cg_alpha): every wave of a block finds the
+// same status and reaches the same barriers.
 template <int EPI, bool SLOT>
 __device__ __forceinline__ bool alpha_block(const DslashArgs &A)
 {
@@ -982,10 +991,10 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
     double kappa = A.kappa_u, a = A.a_u, alpha = 0;
     if constexpr (SLOT) {
         const SlotState &st = A.st[slot];
-        if (st.status != ST_RUNNING) return;  // uniform over the block
+        if (!slot_runs<EPI>(st)) return;  // uniform over the block: nothing it reads is written by this launch
         kappa = st.kappa;
         a = st.a;
-        alpha = st.alpha;
+        if (EPI == EPI_CGUPD) alpha = st.alpha;
     }
     const Geom &g = A.g;
     const int vh = g.vh, lt = g.L[3], tw = A.twalk;
@@ -1188,10 +1197,10 @@ __global__ __launch_bounds__(512, (SP == P64 ? 2 : 4)) void k_dslash_split(const
     double kappa = A.kappa_u, a = A.a_u, alpha = 0;
     if constexpr (SLOT) {
         const SlotState &st = A.st[slot];
-        if (st.status != ST_RUNNING) return;  // uniform over the block
+        if (!slot_runs<EPI>(st)) return;  // uniform over the block: nothing it reads is written by this launch
         kappa = st.kappa;
         a = st.a;
-        alpha = st.alpha;
+        if (EPI == EPI_CGUPD) alpha = st.alpha;
     }
     const Geom &g = A.g;
     const int lane = (int)threadIdx.x & 63, d = (int)threadIdx.x >> 6;

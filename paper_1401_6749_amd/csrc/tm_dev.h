@@ -487,8 +487,6 @@ __device__ __forceinline__ double block_sum(double v, double *lds /* NT/64 doubl
 // (lane l adds v[l + 64 (8 k + j)] in eight running sums j, then the eight in
 // pairs, then the wave) and the step that alpha owes to x.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ bool finite_pos(double v) { return v > 0.0 && v < 1.0e300; }
-
 __device__ __forceinline__ void cg_alpha_wave(SlotState &S, const double *v, int n)
 {
     const int lane = (int)threadIdx.x & 63;
@@ -504,16 +502,7 @@ __device__ __forceinline__ void cg_alpha_wave(SlotState &S, const double *v, int
         for (int j = 0; j < 8; j++)
             if (i0 + 64 * j < n) s[j] += v[i0 + 64 * j];
     const double pap = wave_sum(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])));
-    if (lane != 0) return;
-    S.pap = pap;
-    if (!finite_pos(pap)) {
-        S.status = ST_NUMERIC;
-        S.alpha = 0.0;
-        S.xpend = 0;
-    } else {
-        S.alpha = S.rr / pap;
-        S.xpend = 1;
-    }
+    if (lane == 0) cg_alpha(S, pap);
 }
 
 // XCD-aware block mapping.  Consecutive hardware block ids are dealt out to

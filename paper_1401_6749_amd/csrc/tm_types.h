@@ -95,6 +95,56 @@ struct alignas(128) SlotState {
                       // applied by the direction update at the end of the iteration)
 };
 
+#ifdef __HIPCC__
+#define TM_HD __host__ __device__ inline
+#else
+#define TM_HD inline
+#endif
+
+// The scalar steps of a CG iteration of one running slot.
+//
+// alpha from <p, Ap>.  It runs beside the blocks of the third Dslash, which
+// read status once per wave, so it leaves status alone: a curvature that is
+// not positive and finite shows as an iteration without a step (xpend = 0).
+TM_HD bool finite_pos(double v) { return v > 0.0 && v < 1.0e300; }
+
+TM_HD void cg_alpha(SlotState &S, double pap)
+{
+    const bool ok = finite_pos(pap);
+    S.pap = pap;
+    S.alpha = ok ? S.rr / pap : 0.0;
+    S.xpend = ok ? 1 : 0;
+}
+
+// whether the fourth Dslash, which applies alpha, runs for the slot
+TM_HD bool cg_steps(const SlotState &S) { return S.status == ST_RUNNING && S.xpend != 0; }
+
+// end of the iteration with the new |r|^2 (not read without a step)
+TM_HD void cg_beta(SlotState &S, double rr)
+{
+    if (!S.xpend) {
+        S.status = ST_NUMERIC;
+        return;
+    }
+    S.iter += 1;
+    S.rr_new = rr;
+    if (!(rr >= 0.0 && rr < 1.0e300)) {
+        S.status = ST_NUMERIC;
+    } else if (S.tol2 > 0.0 && rr <= S.tol2 * S.rr0) {
+        // mixed precision confirms convergence on the true residual
+        S.status = S.mixed ? ST_NEED_UPDATE : ST_CONVERGED;
+        if (!S.mixed) S.rr = rr;
+    } else if (S.mixed && rr <= S.delta2 * S.rr_ref) {
+        S.status = ST_NEED_UPDATE;
+    } else if (S.iter >= S.max_iter) {
+        S.status = ST_MAXITER;
+        S.rr = rr;
+    } else {
+        S.beta = rr / S.rr;
+        S.rr = rr;
+    }
+}
+
 // Site-local coefficient sets of the Dslash epilogue out = P*in2 + Q*hop(in),
 // per chirality (spins 0,1 and spins 2,3), built from (kappa, a).
 enum : int {
