@@ -71,7 +71,7 @@ size_t batch_footprint(const tm_gauge *G, Kind kind, int S)
     if (kind == K_MIXED) b += (size_t)S * 2 * half_bytes(P64, g);  // x64, b64
     b += (size_t)S * 2 * g.vh * sizeof(uint32_t);      // noise codes
     b += (lp_kind(kind) ? 4 : 3) * (scratch_bytes(g, kind, S) + 256);  // scratch FA, FB, FC (, FD)
-    b += (size_t)S * ntile_of(g) * sizeof(double) + 4096;
+    b += (size_t)S * ntile_most(g) * sizeof(double) + 4096;
     b += (size_t)(lp_kind(kind) ? S : 1) * contract_part_doubles(g) * sizeof(double) + 256;
     b += (size_t)S * sizeof(SlotState) + 64 * sizeof(double) + 16 * 256;
     return b;
@@ -120,7 +120,9 @@ int batch_create(tm_context *ctx, const tm_gauge *G, Kind kind, int S, int chunk
     b->hsp = slot_pitch(half_bytes(sp, g));
     b->hxr = slot_pitch(half_bytes(b->xr, g));
     b->h64 = half_bytes(P64, g);
-    b->nblk = ntile_of(g);  // per-slot partial sums (64-site tiles)
+    b->nblk = ntile_of(g, sp);
+    b->nblk64 = ntile_of(g, P64);
+    b->npart = ntile_most(g);
     b->bytes = batch_footprint(G, kind, S) + 32 * 256;
     if (mem) b->mem = *mem;
     char *base = (char *)(b->mem.alloc ? b->mem.alloc(b->mem.self, b->bytes) : dalloc(ctx, b->bytes));
@@ -147,7 +149,7 @@ int batch_create(tm_context *ctx, const tm_gauge *G, Kind kind, int S, int chunk
     b->FB = carve(cur, sb);
     b->FC = carve(cur, sb);
     if (lp_kind(kind)) b->FD = carve(cur, sb);
-    b->partial = (double *)carve(cur, (size_t)S * b->nblk * sizeof(double) + 4096);
+    b->partial = (double *)carve(cur, (size_t)S * b->npart * sizeof(double) + 4096);
     b->cpart = (double *)carve(cur, (size_t)(lp_kind(kind) ? S : 1) * contract_part_doubles(g) * sizeof(double));
     b->dres = (double *)carve(cur, 64 * sizeof(double));
     b->st = (SlotState *)carve(cur, (size_t)S * sizeof(SlotState));
@@ -328,7 +330,7 @@ static void fill_noise_run(Batch *b, int s0, int n, Job *const *jobs, int pp)
     const size_t w = n > 1 ? b->wpitch : half_bytes(pq, g);
     char *Be = b->FB, *To = b->FC, *Ce = mixed ? b->b64 + s0 * b->h64 : b->FA;
     const size_t wc = mixed ? b->h64 : w;
-    double *part = b->partial + (size_t)s0 * b->nblk;
+    double *part = b->partial + (size_t)s0 * b->npart;
     dsl_codes_run(b, pq, 3, CM_PREP, 0, s0, n, nullptr, 0, Be, w, kappa, a);
     dsl_run(b, pq, true, EPI_PLAIN, CM_AINV_DAG, 1, Be, w, nullptr, 0, To, w, kappa, a, n);
     // LP runs: the last preparation Dslash writes r = p = rhs and x = 0 in
@@ -354,7 +356,7 @@ static void fill_noise_run(Batch *b, int s0, int n, Job *const *jobs, int pp)
         fused = launch_dslash_start(pq, b->xr, A, s) == 0;
     }
     if (!fused) dsl_run(b, pq, true, EPI_NORM, CM_MHAT_DAG, 0, To, w, Be, w, Ce, wc, kappa, a, n, part);
-    launch_slot_start(b->st + s0, part, b->nblk, P, n, s);
+    launch_slot_start(b->st + s0, part, ntile_of(g, pq), P, n, s);
     if (!fused) {
         if (b->xr == b->sp && b->hxr == b->hsp && (pq == P64 || pq == P32)) {
             launch_cg_start(pq, b->xr, g, Ce, wc, b->r + s0 * b->hxr, b->p + s0 * b->hsp, b->x + s0 * b->hxr, b->hxr,
@@ -396,13 +398,13 @@ static void fill_user_run(Batch *b, int s0, int n, Job *const *jobs)
     const size_t w = pitch64(b, n);
     char *Be = b->FA, *To = b->FB, *Ce = mixed ? b->b64 + s0 * b->h64 : b->FC;
     const size_t wc = mixed ? b->h64 : w;
-    double *part = b->partial + (size_t)s0 * b->nblk;
+    double *part = b->partial + (size_t)s0 * b->npart;
     launch_eta_import(g, n, jobs[0]->b_canon, Be, To, w, true, a, s);
     // bhat over b_e: each site reads its own b_e before it writes
     dsl_run(b, P64, false, EPI_PLAIN, CM_PREP, 0, To, w, Be, w, Be, w, kappa, a, n);
     dsl_run(b, P64, true, EPI_PLAIN, CM_AINV_DAG, 1, Be, w, nullptr, 0, To, w, kappa, a, n);
     dsl_run(b, P64, true, EPI_NORM, CM_MHAT_DAG, 0, To, w, Be, w, Ce, wc, kappa, a, n, part);
-    launch_slot_start(b->st + s0, part, b->nblk, P, n, s);
+    launch_slot_start(b->st + s0, part, b->nblk64, P, n, s);
     launch_cg_start(P64, b->xr, g, Ce, wc, b->r + s0 * b->hxr, b->p + s0 * b->hsp, b->x + s0 * b->hxr, b->hxr, n, s);
     if (mixed) launch_zero(P64, g, b->x64 + s0 * b->h64, b->h64, n, s);
 }
@@ -470,7 +472,7 @@ static void enqueue_iteration(Batch *b)
     A.coef = CM_MHAT;
     launch_dslash(sp, false, EPI_NORM, true, A, b->stream);
     // alpha, beside D3 where the walk serves the lattice
-    const bool beside = walk_plan(b->G->g).tiles > 0;
+    const bool beside = !register_lattice(walk_plan(b->G->g, sp), sp);
     if (!beside) launch_cg_alpha(b->st, b->partial, b->S, b->nblk, b->stream);
     // D3
     A.alpha_blocks = beside ? (b->S + 7) & ~7 : 0;
@@ -550,7 +552,7 @@ static void reliable_update_run(Batch *b, int s0, int n)
     char *x64 = b->x64 + s0 * b->h64;
     char *x32 = b->x + s0 * b->hxr, *r32 = b->r + s0 * b->hxr;
     char *Bo = b->FB, *Be = b->FA, *Ce = b->FC;
-    double *part = b->partial + (size_t)s0 * b->nblk;
+    double *part = b->partial + (size_t)s0 * b->npart;
     launch_accum_x(g, x64, b->h64, x32, x32, b->hxr, n, s);
     dsl_run(b, P64, false, EPI_PLAIN, CM_AINV, 1, x64, b->h64, nullptr, 0, Bo, w, j->kappa, j->a, n);
     dsl_run(b, P64, false, EPI_PLAIN, CM_MHAT, 0, Bo, w, x64, b->h64, Be, w, j->kappa, j->a, n);
@@ -558,7 +560,7 @@ static void reliable_update_run(Batch *b, int s0, int n)
     dsl_run(b, P64, true, EPI_RESID, CM_MHAT_DAG, 0, Bo, w, Be, w, Ce, w, j->kappa, j->a, n, part,
             b->b64 + s0 * b->h64, b->h64);
     launch_convert(P64, b->xr, g, Ce, w, r32, b->hxr, n, s);
-    launch_reliable_finish(b->st + s0, part, b->nblk, n, s);
+    launch_reliable_finish(b->st + s0, part, b->nblk64, n, s);
     launch_p_update(b->sp, b->xr, g, b->p + s0 * b->hsp, b->hsp, r32, b->hxr, nullptr, 0, b->st + s0, n, b->ctx->swz,
                     s);
     for (int i = 0; i < n; i++) b->slot_updates[s0 + i]++;
@@ -657,8 +659,8 @@ static Sol64 sol64(Batch *b, int s0, int n)
 static int true_residual_run(Batch *b, int s0, int n, const Sol64 &s, const char *Ee, const char *Eo, size_t w)
 {
     const Job *j = b->slot_job[s0];
-    double *part = b->partial + (size_t)s0 * b->nblk;
-    auto sum = [&](int k) { launch_reduce(part, b->nblk, n, b->dres + k * MAX_SLOTS, b->stream); };
+    double *part = b->partial + (size_t)s0 * b->npart;
+    auto sum = [&](int k) { launch_reduce(part, b->nblk64, n, b->dres + k * MAX_SLOTS, b->stream); };
     // even: eta_e - (A s_e - kappa D_eo s_o); odd: eta_o - (A s_o - kappa D_oe s_e)
     dsl_run(b, P64, false, EPI_RESID, CM_M, 0, s.so, s.pitch, s.se, s.pitch, nullptr, 0, j->kappa, j->a, n, part, Ee, w);
     sum(0);

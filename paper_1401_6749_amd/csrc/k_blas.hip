@@ -408,7 +408,7 @@ __global__ __launch_bounds__(BLOCK) void k_norm_partial(Geom g, const char *f, s
 
 void launch_norm_partial(const Geom &g, const char *f, size_t pitch, int n, double *partial, hipStream_t s)
 {
-    const int nt = ntile_of(g);
+    const int nt = ntile_of(g, P64);
     hipLaunchKernelGGL(k_norm_partial, dim3((nt * TILE + BLOCK - 1) / BLOCK, n), dim3(BLOCK), 0, s, g, f, pitch,
                        partial, nt);
 }

@@ -13,7 +13,6 @@
 #include "tm_launch.h"
 
 #include <algorithm>
-#include <cmath>
 #include <cstdlib>
 #include <type_traits>
 
@@ -1157,6 +1156,22 @@ __global__ __launch_bounds__(WALK_MAX, (walk_waves<SP, EPI>())) void k_dslash_wa
     }
 }
 
+// Lane's site in a reduction tile of the walk (timeslice, chunk, wave of the
+// chunk); lanes beyond the chunk's last site follow that site and are not live.
+__device__ __forceinline__ int tile_site(const DslashArgs &A, int tile, int lane, bool &live)
+{
+    const Geom &g = A.g;
+    const int ncy = g.L[1] / A.wcy, chunks = ncy * (g.L[2] / A.wcz);
+    const int cs = A.wcy * A.wcz * g.lxh, wpc = (cs + 63) >> 6;
+    const int tc = tile / wpc, t = tc / chunks, c = tc - t * chunks;
+    const int lw = (tile - tc * wpc) * 64 + lane;
+    live = lw < cs;
+    const int l = live ? lw : cs - 1;
+    const int rz = l / g.lxh, xh = l - rz * g.lxh;
+    const int yy = rz % A.wcy, zz = rz / A.wcy;
+    return t * g.st + xh + g.sy * ((c % ncy) * A.wcy + yy) + g.sz * ((c / ncy) * A.wcz + zz);
+}
+
 // ---------------------------------------------------------------------------
 // Small launches: one wave per neighbour direction.
 //
@@ -1204,16 +1219,8 @@ __global__ __launch_bounds__(512, (SP == P64 ? 2 : 4)) void k_dslash_split(const
     }
     const Geom &g = A.g;
     const int lane = (int)threadIdx.x & 63, d = (int)threadIdx.x >> 6;
-    // tile = (timeslice, chunk, wave of the chunk)
-    const int ncy = g.L[1] / A.wcy, chunks = ncy * (g.L[2] / A.wcz);
-    const int cs = A.wcy * A.wcz * g.lxh, wpc = (cs + 63) >> 6;
-    const int tc = tile / wpc, t = tc / chunks, c = tc - t * chunks;
-    const int lw = (tile - tc * wpc) * 64 + lane;
-    const bool live = lw < cs;
-    const int l = live ? lw : cs - 1;
-    const int rz = l / g.lxh, xh = l - rz * g.lxh;
-    const int yy = rz % A.wcy, zz = rz / A.wcy;
-    const int cb = t * g.st + xh + g.sy * ((c % ncy) * A.wcy + yy) + g.sz * ((c / ncy) * A.wcz + zz);
+    bool live;
+    const int cb = tile_site(A, tile, lane, live);
     const Site s = site_of(g, cb, A.out_par);
     HopRes R;
     R.gauge = mkrsrc(A.gauge, A.gauge_span);
@@ -1270,6 +1277,70 @@ __global__ __launch_bounds__(512, (SP == P64 ? 2 : 4)) void k_dslash_split(const
     }
 }
 
+// ---------------------------------------------------------------------------
+// Launches of less than a wave per SIMD: every neighbour from global memory.
+//
+// The walk goes over one timeslice only there, its LDS saves no traffic, and
+// staging two timeslices ahead of the eight neighbours lengthens the chain of
+// latencies that such a launch is (FLAT_BELOW).  Here each wave takes one reduction tile
+// and adds its neighbours one after another, in the walk's order, so outputs
+// and sums have the walk's bits; nothing is shared between the waves.
+// ---------------------------------------------------------------------------
+template <int SP, bool DAG, int EPI, bool IN2, bool SLOT, int SRC = 0, int PO = SP, bool TL = false>
+__global__ __launch_bounds__(BLOCK, dslash_waves<SP>()) void k_dslash_flat(const DslashArgs A0)
+{
+    using T = typename Real<SP>::T;
+    using RawT = typename RawSel<SP, T>::type;
+    int sb, slot;
+    constexpr bool BOTH = EPI == EPI_PLAIN && !SLOT && SRC == 0;
+    if (alpha_block<EPI, SLOT>(A0)) return;
+    const int first = EPI == EPI_PLAIN && SLOT ? A0.alpha_blocks : 0;
+    if (!map_block(BOTH && A0.par_bytes ? 2 * A0.nblk_site : A0.nblk_site, A0.nslot, A0.swz, sb, slot, false, first))
+        return;
+    DslashArgs A = A0;
+    if constexpr (BOTH) sb = pick_parity(A, sb);
+    double kappa = A.kappa_u, a = A.a_u, alpha = 0;
+    if constexpr (SLOT) {
+        const SlotState &st = A.st[slot];
+        if (!slot_runs<EPI>(st)) return;
+        kappa = st.kappa;
+        a = st.a;
+        if (EPI == EPI_CGUPD) alpha = st.alpha;
+    }
+    const int lane = (int)threadIdx.x & 63, tile = sb * (BLOCK / 64) + ((int)threadIdx.x >> 6);
+    if (tile >= A.ntile) return;
+    bool live;
+    const int cb = tile_site(A, tile, lane, live);
+    const Site s = site_of(A.g, cb, A.out_par);
+    HopRes R;
+    R.gauge = mkrsrc(A.gauge, A.gauge_span);
+    R.in = mkrsrc(A.in + (size_t)slot * A.in_slot, A.in_span);
+    R.lane = 0;
+    cpx<T> acc[12];
+#pragma unroll
+    for (int k = 0; k < 12; k++) acc[k] = cpx<T>{(T)0, (T)0};
+    // the stages apart, as in hop_all
+#pragma unroll 1
+    for (int d = 0; d < 8; d++) {
+        switch (__builtin_amdgcn_readfirstlane(TL ? d + 1 : d)) {
+        case 1: hop_dir<T, SP, 0, true, DAG, RawT>(A, R, s, acc, 0.0, 0.0); break;
+        case 2: hop_dir<T, SP, 0, false, DAG, RawT>(A, R, s, acc, 0.0, 0.0); break;
+        case 3: hop_dir<T, SP, 1, true, DAG, RawT>(A, R, s, acc, 0.0, 0.0); break;
+        case 4: hop_dir<T, SP, 1, false, DAG, RawT>(A, R, s, acc, 0.0, 0.0); break;
+        case 5: hop_dir<T, SP, 2, true, DAG, RawT>(A, R, s, acc, 0.0, 0.0); break;
+        case 6: hop_dir<T, SP, 2, false, DAG, RawT>(A, R, s, acc, 0.0, 0.0); break;
+        case 7: hop_dir<T, SP, 3, true, DAG, RawT>(A, R, s, acc, 0.0, 0.0); break;
+        default: hop_dir<T, SP, 3, false, DAG, RawT>(A, R, s, acc, 0.0, 0.0); break;  // 0, or 8 with TL
+        }
+    }
+    double part = 0.0;
+    if (live) part = epilogue<SP, EPI, IN2, SRC, false, PO>(A, slot, cb, acc, kappa, a, alpha);
+    if constexpr (EPI != EPI_PLAIN) {
+        const double v = wave_sum(part);
+        if (lane == 0) A.partial[(size_t)slot * A.ntile + tile] = v;
+    }
+}
+
 template <int SP, bool DAG, int EPI, bool IN2, int R>
 static void launch_r(const DslashArgs &A, hipStream_t s)
 {
@@ -1301,39 +1372,21 @@ inline int lanes_per_site(int nslot)
     return r;
 }
 
-// Timeslices walked per block, a divisor of Lt up to 8 (TM_LDS_TWALK).  A block
-// that walks tw timeslices takes tw + 1 steps (its first loads stage two
-// timeslices), and each of the 256 CUs runs 4 SIMDs x waves at a time, so the
-// walk is the longest that does not lengthen rounds x (tw + 1).  Long walks
-// pay on large launches (12 FP32 right-hand sides at 32^3x64, both parities:
-// 8 / 4 / 2 / 1 timeslices 1688 / 1728 / 1878 / 2225 us); on small ones they
-// leave CUs idle (one FP64 M at 16^3x32: 148 / 78 / 45 / 32 us; 12 FP32
-// right-hand sides: 117 / 87 / 91 / 102 us).  The outputs have the same bits.
-inline int walk_length(const Geom &g, const WalkPlan &p, int nslot, int waves)
-{
-    static const int most = std::max(1, env_knob("TM_LDS_TWALK", 8));
-    const double cap = 256 * std::max(1, 4 * waves / (p.threads / 64));  // blocks at a time
-    double best = 1e30;
-    int len = 1;
-    for (int tw = std::min(most, g.L[3]); tw >= 1; tw--) {
-        if (g.L[3] % tw) continue;
-        double rounds = (double)p.chunks * (g.L[3] / tw) * nslot / cap;
-        if (rounds <= 4.0) rounds = std::ceil(rounds);
-        const double cost = rounds * (tw + 1);
-        if (cost < best - 1e-9) {
-            best = cost;
-            len = tw;
-        }
-    }
-    return len;
-}
-
 // Most reduction tiles x right-hand sides of a launch on k_dslash_split: two
 // blocks per CU.  Both parities of a hop with one FP64 right-hand side: 64 tiles
 // (8^3x16) 10.7 us against the walk's 17.4 us, 384 tiles (12^3x24) 18.5 against
 // 21.2 us; 768 tiles (12 of them at 8^3x16) 26.4 against 21.5 us, as each block
 // then reads its neighbours from L2 where the walk has them in LDS.
 constexpr int SPLIT_MOST = 512;
+
+// Reduction tiles x right-hand sides (waves) of one parity below which FP64 and
+// half precision take k_dslash_flat: less than one wave per SIMD.  Mhat, two such
+// launches, walk against flat: FP64, one right-hand side at 14x22x10x26 (780) 31.0 /
+// 25.1 us, at 14^3x28 (784) 27.2 / 24.0 us, at 16^3x32 (1024) 33.8 / 35.4 us; FP16,
+// three at 12x10x14x18 (756) 20.1 / 17.1 us.  With both parities in one launch,
+// and in FP32, the walk is as fast or faster (FP64 hop at 12^3x24, 768: 11.6 / 11.7 us;
+// FP32 Mhat at 14^3x28 17.7 / 18.2 us).
+constexpr int FLAT_BELOW = 1024;
 
 // Right-hand sides up to which the two parities of a site block run next to
 // each other (on one XCD, in turn): they read the same links, which few
@@ -1344,19 +1397,46 @@ constexpr int SPLIT_MOST = 512;
 // 62.7 us.
 constexpr int PAIR_MOST = 6;
 
+// Half-precision launches without sums on lattices where the register kernel
+// gives the walk's bits (both_t_last), beyond k_dslash_split: whether the register
+// kernel is the faster one.  Walk / register kernel:
+// - one right-hand side and parity are a single round of either, and the walk
+//   stages two timeslices before its first neighbour (Mhat at 14^3x28 16.5 / 15.7,
+//   18^3x36 24.6 / 21.7, 28^4 51.7 / 49.3 us), unless the register kernel walks
+//   timeslices too (24^3x48 53.4 / 66.1);
+// - both parities take the register kernel two launches, which less than a round
+//   of waves does not repay (hop of six at 2x6^2x96 9.9 / 14.7);
+// - else the walk's idle lanes decide, against half of the register kernel's own,
+//   where the right-hand sides do not fill groups of four (hop at 66x34x16^2, 0.69
+//   busy: six 205 / 272, twelve 475 / 440; three at 38^3x8, 0.59 busy, 115 / 94).
+static bool half_on_register(const DslashArgs &A, const WalkPlan &p)
+{
+    const int n = A.nslot;
+    if (n == 1 && !A.par_bytes && A.g.v3h % BLOCK != 0) return true;
+    if (A.par_bytes && p.tiles * n * 2 < 4096) return false;
+    const double groups = n < 3 ? 1.0 : 4.0 * ((n + 3) / 4) / n;
+    return p.busy * (0.5 + 0.5 * groups) < 0.75;
+}
+
 template <int SP, bool DAG, int EPI, bool IN2, int SRC = 0, int PO = SP>
 static bool launch_walk(DslashArgs A, hipStream_t s)
 {
     {
         const uint64_t field = (uint64_t)A.g.vh * (SP == P64 ? 192 : SP == P32 ? 96 : 52);
-        const WalkPlan plan = walk_plan(A.g);
+        const WalkPlan plan = walk_plan(A.g, SP);
         if (!plan.tiles || field >= (1ull << 32)) return false;
+        constexpr bool HALF = SP == P16 || SP == PBF;
+        const bool last = HALF && both_t_last(A.g);
+        if (HALF && EPI == EPI_PLAIN && last && !A.alpha_blocks) {
+            const int npar = A.par_bytes ? 2 : 1;
+            if (plan.tiles * A.nslot * npar > SPLIT_MOST && half_on_register(A, plan)) return false;
+        } else if (register_lattice(plan, SP)) {
+            return false;
+        }
         A.wcy = plan.cy;
         A.wcz = plan.cz;
         const int npar = A.par_bytes ? 2 : 1;
         A.par_pairs = A.nslot <= PAIR_MOST;
-        constexpr bool HALF = SP == P16 || SP == PBF;
-        const bool last = HALF && both_t_last(A.g);
         if (plan.tiles * A.nslot * npar <= SPLIT_MOST) {
             A.in_span = (uint32_t)field;
             A.gauge_span = (uint32_t)std::min<uint64_t>((uint64_t)2 * 4 * A.g.vh * link_bytes(SP), 0xFFFFFFFFull);
@@ -1375,7 +1455,26 @@ static bool launch_walk(DslashArgs A, hipStream_t s)
             else split(std::false_type{});
             return true;
         }
-        const int tw = walk_length(A.g, plan, A.nslot * npar, walk_waves<SP, EPI>());
+        if (SP != P32 && npar == 1 && plan.tiles * A.nslot < FLAT_BELOW) {
+            A.in_span = (uint32_t)field;
+            A.gauge_span = (uint32_t)std::min<uint64_t>((uint64_t)2 * 4 * A.g.vh * link_bytes(SP), 0xFFFFFFFFull);
+            A.nblk_site = (plan.tiles + BLOCK / 64 - 1) / (BLOCK / 64);
+            A.ntile = plan.tiles;
+            const int total = A.nblk_site * A.nslot * npar;
+            const int grid = A.alpha_blocks + (A.swz ? 8 * ((total + 7) / 8) : total);
+            auto flat = [&](auto tl) {
+                constexpr bool TL = decltype(tl)::value;
+                if (A.st)
+                    hipLaunchKernelGGL((k_dslash_flat<SP, DAG, EPI, IN2, PO == SP && SRC == 0, SRC, PO, TL>), dim3(grid),
+                                       dim3(BLOCK), 0, s, A);
+                else
+                    hipLaunchKernelGGL((k_dslash_flat<SP, DAG, EPI, IN2, false, SRC, PO, TL>), dim3(grid), dim3(BLOCK), 0, s, A);
+            };
+            if (HALF && last) flat(std::integral_constant<bool, HALF>{});
+            else flat(std::false_type{});
+            return true;
+        }
+        const int tw = walk_length(A.g, plan, A.nslot * npar, SP, walk_waves<SP, EPI>());
         A.twalk = tw;
         A.in_span = (uint32_t)field;
         A.gauge_span = (uint32_t)std::min<uint64_t>(
@@ -1440,7 +1539,7 @@ static void launch_t(DslashArgs A, hipStream_t s)
     static const int gouter = env_knob("TM_GROUP_OUTER", 0);
     A.gouter = gouter;
     A.nblk_site = tw > 1 ? A.g.vh / spb / tw : (A.g.vh + spb - 1) / spb;
-    A.ntile = ntile_of(A.g);
+    A.ntile = ntile_of(A.g, SP);
     if (R == 1) launch_r<SP, DAG, EPI, IN2, 1>(A, s);
     else if (R == 2) launch_r<SP, DAG, EPI, IN2, 2>(A, s);
     else launch_r<SP, DAG, EPI, IN2, 4>(A, s);
@@ -1479,7 +1578,7 @@ static void launch_src(DslashArgs A, hipStream_t s)
     A.twalk = 1;
     A.gouter = 0;
     A.nblk_site = (A.g.vh + BLOCK - 1) / BLOCK;
-    A.ntile = ntile_of(A.g);
+    A.ntile = ntile_of(A.g, SP);
     A.gauge_span = (uint32_t)std::min<uint64_t>((uint64_t)2 * 4 * A.g.vh * link_bytes(SP), 0xFFFFFFFFull);
     A.in_span = (uint32_t)std::min<uint64_t>((uint64_t)A.g.vh * (SP == P64 ? 192 : SP == P32 ? 96 : 52), 0xFFFFFFFFull);
     const int total = A.nblk_site * A.nslot;

@@ -84,7 +84,8 @@ struct Batch {
     size_t wpitch = 0;        // their slot pitch
     int wslots = 1;           // slots a run may span
     double *partial = nullptr;
-    int nblk = 0;
+    int nblk = 0, nblk64 = 0;  // partial sums per slot in the solve's precision and in FP64
+    int npart = 0;             // room for them in partial
     double *cpart = nullptr;
     double *dres = nullptr;     // small device results
     double *hres = nullptr;     // pinned mirror

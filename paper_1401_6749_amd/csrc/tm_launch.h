@@ -19,35 +19,61 @@ inline int env_knob(const char *name, int dflt)
 
 // Chunk of the timeslice walk: cy rows (y) x cz planes (z) of full x rows with
 // cy | Ly, cz | Lz, one site per thread; the block has whole waves, the lanes
-// beyond the last site idle.  tiles: reduction tiles (one per wave) of a
-// half field, 0 if no chunk fits (a row longer than a block) or the walk is
-// switched off (TM_LDS_WALK=0).
+// beyond the last site idle.  busy: the share of lanes with a site.  tiles:
+// reduction tiles (one per wave) of a half field, 0 if no chunk fits (a row
+// longer than a block) or the walk is switched off (TM_LDS_WALK=0).
 constexpr int WALK_MAX = 256;  // threads per block
 struct WalkPlan {
     int cy = 0, cz = 0, threads = 0, chunks = 0, tiles = 0;
+    double busy = 0.0;
 };
-// The shape with the least modelled time per site: 1 + 0.09 per halo
-// neighbour (2/cy + 2/cz, no term for a dimension the chunk spans), over the
-// share of busy lanes; among equals the largest.  The 0.09 is the measured
-// slope (FP32, 12 right-hand sides, 32^3x64: 840 us at 1.0 halo neighbours per
-// site, 876 us at 1.5); idle lanes cost their issue slots.  It depends on the
-// lattice alone, so a slot's reduction tiles are the same in every batch.
-inline WalkPlan walk_plan(const Geom &g)
+// Waves of the walk on a CU: its launch bounds allow 2 (FP64), 3 (FP32) and 4 per
+// SIMD, and the LDS of a block, which is that of 256 sites, 3 blocks in FP64 and 6
+// otherwise.
+inline int walk_blocks_per_cu(int sp, int waves_per_block, int waves_per_simd)
+{
+    return std::min(sp == P64 ? 3 : 6, std::max(1, 4 * waves_per_simd / waves_per_block));
+}
+// The shape with the least modelled time per site, among equals the largest,
+// then the one with more rows:
+// - 1 + 0.09 per halo neighbour (2/cy + 2/cz, no term for a dimension the chunk
+//   spans): the measured slope (FP32, 12 right-hand sides, 32^3x64: 840 us at 1.0
+//   halo neighbours per site, 876 us at 1.5);
+// - 0.3 of a 128-byte line (8 sites) per run of sites that are consecutive in
+//   memory, unless runs are whole lines; 0.1 in half precision, which is bound
+//   by issue rather than by traffic;
+// - over the share of busy lanes: idle ones cost their issue slots;
+// - over the share of 6 (FP64) or 8 waves that fit a CU: a block of one wave has
+//   the LDS of 256 sites too.
+// All shapes were timed on 38 lattices (12 right-hand sides, Mhat): this choice
+// is within 1.4% (FP64), 1.5% (FP32) and 0.9% (FP16) of the best on average, 13%
+// at worst; by halo and busy lanes alone, 3.6, 2.9 and 2.8%, 51% at worst.
+// FP64 / FP32 / FP16: 2 x 14 -> 14 x 2 at 14^3x28 179 / 79 / 69 -> 148 / 73 / 66 us, 1 x 13
+// -> 13 x 1 at 26^4 1413 / 668 / 401 -> 1093 / 507 / 346 us, 6 x 2 in one wave -> 15 x 2
+// in three at 10x30x26x14 342 / 119 / 128 -> 255 / 103 / 94 us.
+// It depends on lattice and precision alone, so a slot's reduction tiles are the
+// same in every batch.
+inline WalkPlan walk_plan(const Geom &g, int sp)
 {
     static const bool on = env_knob("TM_LDS_WALK", 1) != 0;
     WalkPlan p;
     if (!on) return p;
+    const bool half = sp == P16 || sp == PBF;
     double best = 1e30;
     int sites = 0;
     for (int y = 1; y <= g.L[1]; y++) {
         if (g.L[1] % y) continue;
         for (int z = 1; z <= g.L[2]; z++) {
             const int cs = y * z * g.lxh;
-            if (g.L[2] % z || cs > WALK_MAX) continue;
+            if (cs > WALK_MAX) break;
+            if (g.L[2] % z) continue;
             const int threads = (cs + 63) & ~63;
             const double halo = (y < g.L[1] ? 2.0 / y : 0.0) + (z < g.L[2] ? 2.0 / z : 0.0);
-            const double cost = (1.0 + 0.09 * halo) * threads / cs;
-            if (cost < best - 1e-9 || (cost < best + 1e-9 && cs > sites)) {
+            const int wpb = threads / 64, fit = wpb * walk_blocks_per_cu(sp, wpb, sp == P64 ? 2 : sp == P32 ? 3 : 4);
+            const int run = g.lxh * y * (y == g.L[1] ? z : 1);
+            const double lines = run % 8 ? (half ? 0.1 : 0.3) * 8 / run : 0.0, full = sp == P64 ? 6 : 8;
+            const double cost = (1.0 + 0.09 * halo + lines) * threads / cs * std::max(1.0, full / fit);
+            if (cost < best - 1e-9 || (cost < best + 1e-9 && cs >= sites)) {
                 best = cost;
                 sites = cs;
                 p.cy = y;
@@ -59,7 +85,55 @@ inline WalkPlan walk_plan(const Geom &g)
     if (!sites) return p;
     p.chunks = (g.L[1] / p.cy) * (g.L[2] / p.cz);
     p.tiles = p.chunks * (p.threads / 64) * g.L[3];
+    p.busy = (double)sites / p.threads;
     return p;
+}
+
+// Lattices that the register kernel, which has no idle lanes, serves instead: few
+// busy lanes, and too many tiles for one wave per neighbour direction.  Mhat, 12
+// right-hand sides, register kernel / walk: FP16, 0.53 busy (34^3x8), 245 / 368 us;
+// 0.69 (66x34x16^2) 465 / 503; 0.72 (46^3x8) 634 / 757; 0.80 (102x22^2x8) 326 / 301.
+// FP64, 0.53 busy, 903 / 1025; 0.59 (38^3x8) 1280 / 1300, but one right-hand side
+// 134 / 112.  FP32, 0.53 busy, 457 / 411.
+inline bool register_lattice(const WalkPlan &p, int sp)
+{
+    return !p.tiles || (p.tiles > 128 && p.busy < (sp == P64 ? 0.55 : sp == P32 ? 0.0 : 0.75));
+}
+
+// Timeslices walked per block, a divisor of Lt up to 8 (TM_LDS_TWALK), for n
+// right-hand sides and parities, waves of the kernel per SIMD.  A block that
+// walks tw timeslices takes tw steps and a shorter one that stages the first
+// two (0.3 of a step).  The busiest of the 256 CUs runs its blocks in rounds of
+// as many as fit; a round takes one step's latency per step, or longer
+// where more waves are resident than it takes to keep the SIMDs issuing (FP64 6,
+// FP32 8, half 16 per CU).  Lengths 1 to 8 were timed on 22 lattices from 6^3x12
+// to 46^3x8 with 1, 3 and 12 right-hand sides: this rule's choice is within 0.9%
+// (FP64), 0.8% (FP32) and 1.3% (FP16) of the best on average, 12, 7 and 16% at
+// worst; with a whole step for the first two timeslices and rounds that all
+// cost the same, 2.7, 1.4 and 3.0%, 36, 10 and 30% at worst (three FP16
+// right-hand sides at 46^3x8: 2 timeslices 186 us, 8 of them 241 us).  The
+// outputs have the same bits.
+inline int walk_length(const Geom &g, const WalkPlan &p, int n, int sp, int waves)
+{
+    static const int most = std::max(1, env_knob("TM_LDS_TWALK", 8));
+    const int wpb = p.threads / 64, fit = walk_blocks_per_cu(sp, wpb, waves);
+    const double sat = sp == P64 ? 6 : sp == P32 ? 8 : 16;
+    const int exact = sp == P16 || sp == PBF ? 4 : 8;  // rounds beyond which the blocks of a CU even out
+    auto round = [&](double blocks) { return std::max(1.0, blocks * wpb / sat); };
+    double best = 1e30;
+    int len = 1;
+    for (int tw = std::min(most, g.L[3]); tw >= 1; tw--) {
+        if (g.L[3] % tw) continue;
+        const long blocks = (long)p.chunks * (g.L[3] / tw) * n, q = (blocks + 255) / 256;
+        const double rounds = q > (long)exact * fit ? round(fit) * blocks / 256 / fit
+                                                    : q / fit * round(fit) + (q % fit ? round(q % fit) : 0.0);
+        const double cost = rounds * (tw + 0.3);
+        if (cost < best - 1e-9) {
+            best = cost;
+            len = tw;
+        }
+    }
+    return len;
 }
 
 // Order of the eight neighbours in half precision: a lattice with a chunk of
@@ -70,9 +144,9 @@ inline WalkPlan walk_plan(const Geom &g)
 inline bool both_t_last(const Geom &g)
 {
     for (int y = 1; y <= g.L[1]; y++)
-        for (int z = 1; g.L[1] % y == 0 && z <= g.L[2]; z++) {
+        for (int z = 1; g.L[1] % y == 0 && z <= g.L[2] && y * z * g.lxh <= WALK_MAX; z++) {
             const int cs = y * z * g.lxh;
-            if (g.L[2] % z == 0 && cs <= WALK_MAX && cs % 64 == 0 && (y == g.L[1] || (y * g.lxh) % 64 == 0)) return false;
+            if (g.L[2] % z == 0 && cs % 64 == 0 && (y == g.L[1] || (y * g.lxh) % 64 == 0)) return false;
         }
     return true;
 }
@@ -140,7 +214,7 @@ void launch_cg_start(int pin, int pout, const Geom &g, const char *in, size_t in
 // x64 += x32; x32 = 0 (if x32_zero), n consecutive slots with strides s64, s32
 void launch_accum_x(const Geom &g, char *x64, size_t s64, const char *x32_in, char *x32_zero, size_t s32, int n,
                     hipStream_t s);
-// |f|^2 partials (ntile_of per field) of n FP64 half fields, pitch bytes apart
+// |f|^2 partials (ntile_of(g, P64) per field) of n FP64 half fields, pitch bytes apart
 void launch_norm_partial(const Geom &g, const char *f, size_t pitch, int n, double *partial, hipStream_t s);
 
 // ---- noise ----
@@ -228,11 +302,18 @@ inline size_t link_array_bytes(int p, const Geom &g)
 }
 __host__ __device__ inline int nblk_of(const Geom &g) { return (g.vh + BLOCK - 1) / BLOCK; }
 // per-slot partial sums: one per wave of the timeslice walk, or per 64-site
-// tile where no chunk fits
-inline int ntile_of(const Geom &g)
+// tile of the register kernel
+inline int ntile_of(const Geom &g, int sp)
 {
-    const WalkPlan p = walk_plan(g);
-    return p.tiles ? p.tiles : (g.vh + TILE - 1) / TILE;
+    const WalkPlan p = walk_plan(g, sp);
+    return register_lattice(p, sp) ? (g.vh + TILE - 1) / TILE : p.tiles;
+}
+// the largest count of any precision
+inline int ntile_most(const Geom &g)
+{
+    int n = 0;
+    for (int sp : {P64, P32, P16, PBF}) n = std::max(n, ntile_of(g, sp));
+    return n;
 }
 
 }  // namespace tmk
