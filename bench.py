@@ -153,7 +153,7 @@ def measure_roofline(torch, tm, inputs, ctx, g, W, workload):
             tr = json.load(f)
         if tr.get("kernel_hash") == khash and tr.get("workload") == workload and tr.get("nrhs") == nrhs:
             traffic = tr.get("hbm_bytes_per_launch")
-    log(f"dslash {prec} x{nrhs}: {t_launch * 1e6:.1f} us/launch, {achieved:.0f} GB/s; copy {copy_gbs:.0f} GB/s")
+    log(f"dslash {prec} x{nrhs}: {t_launch * 1e6:.1f} us per parity, {achieved:.0f} GB/s; copy {copy_gbs:.0f} GB/s")
     return {
         "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
@@ -169,9 +169,10 @@ def measure_roofline(torch, tm, inputs, ctx, g, W, workload):
 
 
 def kernel_rates(torch, tm, inputs, ctx, g, W):
-    """Hop launches in each storage precision (single RHS and 12 RHS at the
-    solver's slot pitch): microseconds per launch and algorithmic GB/s
-    (8 links + 2 spinors per output site and RHS, links once per launch)."""
+    """The hop in each storage precision (single RHS and 12 RHS at the solver's
+    slot pitch): algorithmic GB/s (8 links + 2 spinors per output site and
+    RHS, links once per parity).  One launch covers both output parities;
+    launch_us is the time per parity, half of a launch's."""
     dims = W["dims"]
     vh = dims[0] * dims[1] * dims[2] * dims[3] // 2
     psi = tm.canonical_to_torch(inputs.random_spinor(dims, 2)[None])

@@ -73,7 +73,7 @@ size_t batch_footprint(const tm_gauge *G, Kind kind, int S)
     b += (lp_kind(kind) ? 4 : 3) * (scratch_bytes(g, kind, S) + 256);  // scratch FA, FB, FC (, FD)
     b += (size_t)S * ntile_most(g) * sizeof(double) + 4096;
     b += (size_t)(lp_kind(kind) ? S : 1) * contract_part_doubles(g) * sizeof(double) + 256;
-    b += (size_t)S * sizeof(SlotState) + 64 * sizeof(double) + 16 * 256;
+    b += (size_t)S * sizeof(SlotState) + 4 * MAX_SLOTS * sizeof(double) + 16 * 256;
     return b;
 }
 
@@ -151,7 +151,7 @@ int batch_create(tm_context *ctx, const tm_gauge *G, Kind kind, int S, int chunk
     if (lp_kind(kind)) b->FD = carve(cur, sb);
     b->partial = (double *)carve(cur, (size_t)S * b->npart * sizeof(double) + 4096);
     b->cpart = (double *)carve(cur, (size_t)(lp_kind(kind) ? S : 1) * contract_part_doubles(g) * sizeof(double));
-    b->dres = (double *)carve(cur, 64 * sizeof(double));
+    b->dres = (double *)carve(cur, 4 * MAX_SLOTS * sizeof(double));
     b->st = (SlotState *)carve(cur, (size_t)S * sizeof(SlotState));
     b->stream = stream;
     b->slot_job.assign(S, nullptr);
@@ -159,7 +159,7 @@ int batch_create(tm_context *ctx, const tm_gauge *G, Kind kind, int S, int chunk
     b->slot_pending_update.assign(S, 0);
     b->chunk = chunk > 0 ? chunk : auto_chunk(G, kind, S);
     hipError_t e = hipHostMalloc((void **)&b->st_h, (size_t)S * sizeof(SlotState), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void **)&b->hres, 64 * sizeof(double), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc((void **)&b->hres, 4 * MAX_SLOTS * sizeof(double), hipHostMallocDefault);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev, hipEventDisableTiming);
     if (e != hipSuccess) {
         batch_destroy(b);

@@ -125,19 +125,6 @@ void launch_slot_start(SlotState *st, const double *partial, int nblk, const Slo
     if (n > 0) hipLaunchKernelGGL(k_slot_start, dim3(n), dim3(BLOCK), 0, s, st, partial, nblk, P);
 }
 
-void launch_slot_start(SlotState *st, const double *partial, int nblk, double kappa, double a, double tol2,
-                       int max_iter, double delta2, int mixed, hipStream_t s)
-{
-    SlotStartParams P{};
-    P.kappa[0] = kappa;
-    P.a[0] = a;
-    P.tol2[0] = tol2;
-    P.delta2[0] = delta2;
-    P.max_iter[0] = max_iter;
-    P.mixed = mixed;
-    launch_slot_start(st, partial, nblk, P, 1, s);
-}
-
 void launch_reliable_finish(SlotState *st, const double *partial, int nblk, int n, hipStream_t s)
 {
     if (n > 0) hipLaunchKernelGGL(k_reliable_finish, dim3(n), dim3(BLOCK), 0, s, st, partial, nblk);

@@ -759,10 +759,10 @@ __global__ __launch_bounds__(BLOCK, dslash_waves<SP>()) void k_dslash(const Dsla
 
 
 // ---------------------------------------------------------------------------
-// Timeslice walk through LDS (FP32 and half storage, one slot per block).
+// Timeslice walk through LDS (one slot per block).
 //
 // A block owns a chunk of one timeslice, cy rows (y) x cz planes (z) of full
-// x rows, one site per thread (at most walk_max), for one right-hand side and
+// x rows, one site per thread (at most WALK_MAX), for one right-hand side and
 // walks tw consecutive timeslices.
 // Every input site the walk touches is read from HBM (or L2) once: at each
 // step the thread loads its own site of timeslice t+1, which is at once its
@@ -1185,13 +1185,12 @@ __device__ __forceinline__ int tile_site(const DslashArgs &A, int tile, int lane
 // order (backward t, x, y, z, forward t; with TL both t last) and runs the
 // epilogue.  Outputs and sums have the walk's bits.
 // ---------------------------------------------------------------------------
-template <class T, int SP, int MU, bool FWD, bool DAG, class RawT>
-__device__ __forceinline__ void split_dir(const DslashArgs &A, const HopRes &R, const Site &s, double den, double a,
-                                          cpx<T> w[6])
+template <class T, int SP, int MU, bool FWD, bool DAG>
+__device__ __forceinline__ void split_dir(const DslashArgs &A, const HopRes &R, const Site &s, cpx<T> w[6])
 {
+    using RawT = typename RawSel<SP, T>::type;
     const int n = nbr<MU, FWD ? 1 : -1>(A.g, s);
     RawT raw;
-    raw_setup(raw, den, a);
     raw.load(R.in, 0, A.g.vh, n);
     hop_w<T, SP, MU, FWD, DAG, RawT>(A, R.gauge, s, n, raw, w);
 }
@@ -1224,25 +1223,18 @@ __global__ __launch_bounds__(512, (SP == P64 ? 2 : 4)) void k_dslash_split(const
     const Site s = site_of(g, cb, A.out_par);
     HopRes R;
     R.gauge = mkrsrc(A.gauge, A.gauge_span);
+    R.in = mkrsrc(A.in + (size_t)slot * A.in_slot, A.in_span);
     R.lane = 0;
-    double den = 0.0;
-    if constexpr (SRC & 1) {
-        R.in = mkrsrc(A.codes + (size_t)slot * A.codes_slot / 4 + (size_t)(1 - A.out_par) * g.vh, (uint32_t)g.vh * 4u);
-        den = 1.0 / (1.0 + a * a);
-    } else {
-        R.in = mkrsrc(A.in + (size_t)slot * A.in_slot, A.in_span);
-    }
-    using RawT = typename std::conditional<(SRC & 1) != 0, RawZ4<T>, typename RawSel<SP, T>::type>::type;
     cpx<T> w[6];
     switch (__builtin_amdgcn_readfirstlane(d)) {
-    case 0: split_dir<T, SP, 3, false, DAG, RawT>(A, R, s, den, a, w); break;
-    case 1: split_dir<T, SP, 0, true, DAG, RawT>(A, R, s, den, a, w); break;
-    case 2: split_dir<T, SP, 0, false, DAG, RawT>(A, R, s, den, a, w); break;
-    case 3: split_dir<T, SP, 1, true, DAG, RawT>(A, R, s, den, a, w); break;
-    case 4: split_dir<T, SP, 1, false, DAG, RawT>(A, R, s, den, a, w); break;
-    case 5: split_dir<T, SP, 2, true, DAG, RawT>(A, R, s, den, a, w); break;
-    case 6: split_dir<T, SP, 2, false, DAG, RawT>(A, R, s, den, a, w); break;
-    default: split_dir<T, SP, 3, true, DAG, RawT>(A, R, s, den, a, w); break;
+    case 0: split_dir<T, SP, 3, false, DAG>(A, R, s, w); break;
+    case 1: split_dir<T, SP, 0, true, DAG>(A, R, s, w); break;
+    case 2: split_dir<T, SP, 0, false, DAG>(A, R, s, w); break;
+    case 3: split_dir<T, SP, 1, true, DAG>(A, R, s, w); break;
+    case 4: split_dir<T, SP, 1, false, DAG>(A, R, s, w); break;
+    case 5: split_dir<T, SP, 2, true, DAG>(A, R, s, w); break;
+    case 6: split_dir<T, SP, 2, false, DAG>(A, R, s, w); break;
+    default: split_dir<T, SP, 3, true, DAG>(A, R, s, w); break;
     }
 #pragma unroll
     for (int k = 0; k < 6; k++) half[d][k][lane] = w[k];
@@ -1565,10 +1557,10 @@ static void launch_sp(bool dag, int epi, bool in2, const DslashArgs &A, hipStrea
 #undef TMK_CASE
 }
 
-// Z4-code sources (prep and reconstruction of noise solves), FP32 and FP64.
-// The reconstruction (hop input a field, site-local input the codes) runs on
-// the timeslice walk where a chunk fits; the preparation (hop input decoded
-// from codes) and small lattices on the register kernel.
+// Z4-code sources (prep and reconstruction of noise solves).  The reconstruction
+// (FP32 and FP64, hop input a field, site-local input the codes) runs like the
+// plain operators; the preparation (hop input decoded from codes) on the
+// register kernel.
 template <int SP, int SRC>
 static void launch_src(DslashArgs A, hipStream_t s)
 {

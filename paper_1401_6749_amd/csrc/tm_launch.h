@@ -196,8 +196,6 @@ struct SlotStartParams {
 };
 void launch_slot_start(SlotState *st, const double *partial, int nblk, const SlotStartParams &P, int n,
                        hipStream_t s);
-void launch_slot_start(SlotState *st, const double *partial, int nblk, double kappa, double a, double tol2,
-                       int max_iter, double delta2, int mixed, hipStream_t s);
 // after FP64 reliable updates of n consecutive slots: rr_true = sum(partial);
 // decide convergence, set beta
 void launch_reliable_finish(SlotState *st, const double *partial, int nblk, int n, hipStream_t s);
