@@ -1030,6 +1030,7 @@ int tsm_run(tm_context *ctx, const tm_gauge *G, const tm_tsm_params *P, double *
         std::vector<Job *> part(ql.begin() + ql.size() * k / nlb, ql.begin() + ql.size() * (k + 1) / nlb);
         rc = add(kind_of(P->lp), P->lp, part);
     }
+    for (Batch *B : bs) B->beside = bs.size() > 1;
     if (!rc) rc = run_jobs(bs, qs);
     double hp_end = 0, lp_end = 0;
     for (Batch *B : bs) {

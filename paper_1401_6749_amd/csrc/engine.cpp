@@ -225,6 +225,7 @@ static DslashArgs dargs(const Batch *b, int sp)
     A.gauge = b->G->links[sp];
     A.nslot = 1;
     A.swz = b->ctx->swz;
+    A.beside = b->beside ? 1 : 0;
     return A;
 }
 

@@ -1466,7 +1466,7 @@ static bool launch_walk(DslashArgs A, hipStream_t s)
             else flat(std::false_type{});
             return true;
         }
-        const int tw = walk_length(A.g, plan, A.nslot * npar, SP, walk_waves<SP, EPI>());
+        const int tw = walk_length(A.g, plan, A.nslot * npar, SP, walk_waves<SP, EPI>(), A.beside != 0);
         A.twalk = tw;
         A.in_span = (uint32_t)field;
         A.gauge_span = (uint32_t)std::min<uint64_t>(

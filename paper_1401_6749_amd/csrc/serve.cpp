@@ -67,6 +67,7 @@ struct HipDev {
             delete B;
             return nullptr;
         }
+        B->b->beside = true;
         return B;
     }
     void batch_destroy(Batch *B)

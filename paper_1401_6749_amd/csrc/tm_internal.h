@@ -86,6 +86,7 @@ struct Batch {
     double *partial = nullptr;
     int nblk = 0, nblk64 = 0;  // partial sums per slot in the solve's precision and in FP64
     int npart = 0;             // room for them in partial
+    bool beside = false;       // other batches run at the same time
     double *cpart = nullptr;
     double *dres = nullptr;     // small device results
     double *hres = nullptr;     // pinned mirror

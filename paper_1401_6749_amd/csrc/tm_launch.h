@@ -111,15 +111,21 @@ inline bool register_lattice(const WalkPlan &p, int sp)
 // (FP64), 0.8% (FP32) and 1.3% (FP16) of the best on average, 12, 7 and 16% at
 // worst; with a whole step for the first two timeslices and rounds that all
 // cost the same, 2.7, 1.4 and 3.0%, 36, 10 and 30% at worst (three FP16
-// right-hand sides at 46^3x8: 2 timeslices 186 us, 8 of them 241 us).  The
-// outputs have the same bits.
-inline int walk_length(const Geom &g, const WalkPlan &p, int n, int sp, int waves)
+// right-hand sides at 46^3x8: 2 timeslices 186 us, 8 of them 241 us).
+// beside: the kernels of another batch run at the same time, so latency hides
+// behind them and the work counts: FP64 walks then pay a whole step for the
+// first two timeslices and the same for every round (12 FP64 solves beside four
+// mixed ones at 16^3x32, truncated-solver estimate: 8 timeslices 52.6 ms, 2 of
+// them 53.7; alone 15.9 and 15.1).  FP32 and half precision gained nothing by it.
+// The outputs have the same bits.
+inline int walk_length(const Geom &g, const WalkPlan &p, int n, int sp, int waves, bool beside)
 {
     static const int most = std::max(1, env_knob("TM_LDS_TWALK", 8));
     const int wpb = p.threads / 64, fit = walk_blocks_per_cu(sp, wpb, waves);
     const double sat = sp == P64 ? 6 : sp == P32 ? 8 : 16;
     const int exact = sp == P16 || sp == PBF ? 4 : 8;  // rounds beyond which the blocks of a CU even out
-    auto round = [&](double blocks) { return std::max(1.0, blocks * wpb / sat); };
+    const bool work = beside && sp == P64;
+    auto round = [&](double blocks) { return work ? 1.0 : std::max(1.0, blocks * wpb / sat); };
     double best = 1e30;
     int len = 1;
     for (int tw = std::min(most, g.L[3]); tw >= 1; tw--) {
@@ -127,7 +133,7 @@ inline int walk_length(const Geom &g, const WalkPlan &p, int n, int sp, int wave
         const long blocks = (long)p.chunks * (g.L[3] / tw) * n, q = (blocks + 255) / 256;
         const double rounds = q > (long)exact * fit ? round(fit) * blocks / 256 / fit
                                                     : q / fit * round(fit) + (q % fit ? round(q % fit) : 0.0);
-        const double cost = rounds * (tw + 0.3);
+        const double cost = rounds * (tw + (work ? 1.0 : 0.3));
         if (cost < best - 1e-9) {
             best = cost;
             len = tw;
